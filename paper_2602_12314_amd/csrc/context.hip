@@ -151,15 +151,15 @@ bool ctx_ok(const lam_ctx* ctx)
     return hipGetDevice(&dev) == hipSuccess && dev == ctx->device;
 }
 
-int ctx_resident_blocks(lam_ctx* ctx, const void* kernel, int threads)
+int ctx_resident_blocks(lam_ctx* ctx, const void* kernel, int threads, size_t lds)
 {
     std::lock_guard<std::mutex> lk(ctx->mu);
     for (const auto& e : ctx->occ)
-        if (e.kernel == kernel && e.threads == threads) return e.blocks;
+        if (e.kernel == kernel && e.threads == threads && e.lds == lds) return e.blocks;
     int per = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, 0) != hipSuccess) per = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, lds) != hipSuccess) per = 1;
     const int n = std::max(1, std::max(ctx->cus, 1) * std::max(per, 1));
-    ctx->occ.push_back(lam_ctx::Occ{kernel, threads, n});
+    ctx->occ.push_back(lam_ctx::Occ{kernel, threads, n, lds});
     return n;
 }
 

@@ -41,6 +41,7 @@ struct lam_ctx {
     struct Occ {
         const void* kernel;
         int threads, blocks;
+        size_t lds;
     };
     std::vector<Occ> occ;
     struct Lds {
@@ -64,9 +65,9 @@ bool ctx_ok(const lam_ctx* ctx);
 // The options of ``ctx``, or the defaults when it is null (the host-only
 // size queries accept a null context).
 const lam_ctx* ctx_options(const lam_ctx* ctx);
-// Workgroups of ``kernel`` with ``threads`` threads resident on the device at
+// Workgroups of ``kernel`` with ``threads`` threads and ``lds`` bytes of dynamic LDS resident on the device at
 // once (cached in the context).
-int ctx_resident_blocks(lam_ctx* ctx, const void* kernel, int threads);
+int ctx_resident_blocks(lam_ctx* ctx, const void* kernel, int threads, size_t lds);
 // Raises the dynamic LDS limit of ``kernel`` to at least ``bytes`` once per
 // context (a function attribute of the device).
 hipError_t ctx_ensure_lds(lam_ctx* ctx, const void* kernel, size_t bytes);

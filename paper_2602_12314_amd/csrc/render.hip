@@ -290,22 +290,129 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ key
     }
 }
 
-// ------------------------------------------------------------- raster fwd
+// ------------------------------------------------------ compositing: blocks
 
-constexpr int kChunk = 256;
+// The compositing kernels work wave by wave: a wave owns a block of 64 pixels
+// of its tile (8 x 8 where the tile is at least that in both directions; lane
+// p is pixel (p % bw, p / bw) of it) and walks the tile's list by itself, with
+// no barrier.  It takes the list 64 entries at a time, one per lane: the lane
+// builds the 64-bit mask of the block's pixels inside its entry's footprint
+// and drops the entry when the footprint misses the block or no pixel of the
+// block can reach the alpha threshold (block_reached).  Only the entries that
+// are left are visited, by all lanes, in list order.
+//
+// The sums over the query channels run on the matrix cores in float32: the
+// blend acc[pixel][k] += w[pixel] q[k] as a K = 1 outer product (lane = pixel
+// on one side, lane = channel on the other), and in the backward the dot
+// products q . dQ and the sums over the pixels as K = 4 products.  With one
+// lane per pixel and the channels in registers, the same sums read every
+// channel of every entry through LDS broadcasts (8 cycles of the CU's one LDS
+// pipe per 16 bytes and wave, so the forward was bound by LDS: 106 us at
+// 640x480, 333 us for the 2M-Gaussian keyframe) and the backward spent some
+// 180 of its 250 vector operations per entry on channels and wave sums.
 
-// RGBD: each staged entry also carries (colour r, g, b, camera-space depth z)
-// of its record, blended with the same weights as the query (Eq. 2: colour;
-// depth by the same alpha blending).
-template <int DQ, bool RGBD>
-struct TileStage {
-    float4 r0[kChunk];
-    float4 r1[kChunk];
-    uint2 fp[kChunk];
-    uint32_t rec[kChunk];
-    float q[kChunk * DQ];
-    float4 x[RGBD ? kChunk : 1];
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kList = 64;  // list entries taken at a time, one per lane
+
+// The wave's block of the tile: x0, y0 its first pixel, width 1 << sx.
+// rows has the bit of each row's first pixel.
+struct Block {
+    int x0, y0, sx, w, h;
+    unsigned long long rows;
 };
+
+// LDS written by some lanes of the wave is read by others after this (one
+// wave's LDS operations complete in order: it only holds the compiler back).
+__device__ inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ inline Block wave_block(const CamSet& cs, const Cam& cam, int tile)
+{
+    const int lt = tile - cam.tile_base;
+    const int tyi = lt / cam.tiles_x, txi = lt - tyi * cam.tiles_x;
+    Block b;
+    b.sx = min(6 - min(3, cs.tile_shift_y), cs.tile_shift_x);
+    b.w = 1 << b.sx;
+    b.h = kWave >> b.sx;
+    const int nx = cs.tile_shift_x - b.sx;  // log2 of the blocks per tile row
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    b.x0 = (txi << cs.tile_shift_x) + ((w & ((1 << nx) - 1)) << b.sx);
+    b.y0 = (tyi << cs.tile_shift_y) + (w >> nx) * b.h;
+    b.rows = 0ull;
+    for (int y = 0; y < b.h; ++y) b.rows |= 1ull << (y << b.sx);
+    return b;
+}
+
+// Mask of the block's pixels (bit = lane) inside footprint f.
+__device__ inline unsigned long long block_mask(const Block& b, uint2 f)
+{
+    const int xa = max((int)(f.x & 0xFFFF) - b.x0, 0), xb = min((int)(f.x >> 16) - b.x0, b.w - 1);
+    const int ya = max((int)(f.y & 0xFFFF) - b.y0, 0), yb = min((int)(f.y >> 16) - b.y0, b.h - 1);
+    if (xa > xb || ya > yb) return 0ull;
+    const unsigned long long cols = (2ull << xb) - (1ull << xa);
+    return (cols * b.rows) & ((2ull << (((yb + 1) << b.sx) - 1)) - (1ull << (ya << b.sx)));
+}
+
+// o G(p) of one pair.  Both directions take their decisions (alpha threshold,
+// clamp, termination) from these float32 steps, written out so that they
+// round alike wherever they are inlined.
+__device__ inline float pair_og(float u, float v, float A, float B, float C, float o, float px, float py)
+{
+#pragma clang fp contract(off)
+    const float dx = u - px, dy = v - py;
+    const float q = fmaf(dx, dx * A, dy * (dy * C));
+    const float power = fmaf(q, -0.5f, -(dy * (dx * B)));
+    return o * __builtin_amdgcn_exp2f(power * 1.44269504f);
+}
+
+// False only when every pixel of the block has o G < 1/255: the least of
+// q(dx, dy) = A dx^2 + 2 B dx dy + C dy^2 over the block's rectangle (zero if
+// it holds the centre, else on one of its edges) is compared with
+// 2 ln(255 o).  The slack covers the rounding of pair_og (a few ulp of the
+// terms of q, which may cancel) many times over; anything undecided (NaN, a
+// conic that is not positive definite) is kept.
+__device__ inline bool block_reached(const Block& b, float u, float v, float A, float B, float C, float o)
+{
+    const float xl = u - (float)(b.x0 + b.w - 1), xh = u - (float)b.x0;
+    const float yl = v - (float)(b.y0 + b.h - 1), yh = v - (float)b.y0;
+    if (!(A > 0.0f && C > 0.0f && A * C > B * B)) return true;
+    if (xl <= 0.0f && xh >= 0.0f && yl <= 0.0f && yh >= 0.0f) return true;
+    const float ra = -B * __builtin_amdgcn_rcpf(A), rc = -B * __builtin_amdgcn_rcpf(C);
+    auto q = [&](float x, float y) { return A * x * x + 2.0f * B * x * y + C * y * y; };
+    auto cl = [](float x, float lo, float hi) { return fminf(fmaxf(x, lo), hi); };
+    const float m = fminf(fminf(q(xl, cl(rc * xl, yl, yh)), q(xh, cl(rc * xh, yl, yh))),
+                          fminf(q(cl(ra * yl, xl, xh), yl), q(cl(ra * yh, xl, xh), yh)));
+    const float xm = fmaxf(xl * xl, xh * xh), ym = fmaxf(yl * yl, yh * yh);
+    const float lim = 1.38629436f * __builtin_amdgcn_logf(255.0f * o);  // log2
+    return !(m > lim + 0.02f + 1e-5f * (A * xm + C * ym));
+}
+
+// One list entry as its lane loads it.
+struct Entry {
+    uint32_t rec;
+    float u, v;
+    float4 con;  // A, B, C, opacity
+    uint2 fp;
+};
+
+__device__ inline Entry load_entry(uint32_t r, const float4* __restrict__ rec0, const float4* __restrict__ rec1,
+                                   const uint2* __restrict__ foot)
+{
+    Entry e;
+    e.rec = r;
+    const float2 uv = *reinterpret_cast<const float2*>(rec0 + r);
+    e.u = uv.x;
+    e.v = uv.y;
+    e.con = rec1[r];
+    e.fp = foot[r];
+    return e;
+}
 
 // Colour and depth of one record; the depth is the float32 camera-space z the
 // depth sort keys hold (positive, so its bits are the key).
@@ -316,106 +423,159 @@ __device__ inline float4 rgbz(const float* __restrict__ colors, const uint32_t* 
                        __uint_as_float(depth_key[r]));
 }
 
-template <int DQ, bool RGBD>
-__device__ inline void stage_chunk(TileStage<DQ, RGBD>& st, int k, uint32_t end, int base_tile_c,
-                                   int N, const uint32_t* __restrict__ tile_recs,
-                                   const float4* __restrict__ rec0,
-                                   const float4* __restrict__ rec1,
-                                   const uint2* __restrict__ foot,
-                                   const float* __restrict__ queries,
-                                   const float* __restrict__ colors,
-                                   const uint32_t* __restrict__ depth_key)
-{
-    const int t = threadIdx.x;
-    if ((uint32_t)k < end) {
-        const uint32_t r = tile_recs[k];
-        st.r0[t] = rec0[r];
-        st.r1[t] = rec1[r];
-        st.fp[t] = foot[r];
-        st.rec[t] = r;
-        const uint32_t g = r - (uint32_t)base_tile_c * (uint32_t)N;
-        const float4* qs = reinterpret_cast<const float4*>(queries + (size_t)g * DQ);
-        float4* qd = reinterpret_cast<float4*>(st.q + t * DQ);
-#pragma unroll
-        for (int j = 0; j < DQ / 4; ++j) qd[j] = qs[j];
-        if constexpr (RGBD) st.x[t] = rgbz(colors, depth_key, r, g);
-    }
-}
+// ------------------------------------------------------------- raster fwd
 
+// Entries left of the 64 a wave holds, in list order: (u, v, A, B),
+// (C, opacity, list position + 1, -), the pixel mask and the query row; with
+// RGBD also (colour r, g, b, camera-space depth z), blended with the same
+// weights (Eq. 2: colour; depth by the same alpha blending).
+template <int DQ, bool RGBD>
+struct FwdStage {
+    float4 ab[kList];
+    float4 cd[kList];
+    uint2 mask[kList];
+    float q[kList * DQ];
+    float4 x[RGBD ? kList : 1];
+};
+
+// Per entry and wave the VALU takes some 25 operations (mask, alpha, T) and the
+// matrix cores 32 cycles per 16 channels, beside it.  The K = 1 product adds
+// w q to each channel by one fused multiply-add per entry, in list order, so
+// Q is what a chain of them per pixel gives.
 template <int DQ, bool RGBD>
 __device__ inline void raster_fwd_tile(
-    TileStage<DQ, RGBD>& st, const int tile, const CamSet& cs, int N, const uint2* __restrict__ ranges,
+    FwdStage<DQ, RGBD>& st, const int tile, const CamSet& cs, int N, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ tile_recs, const float4* __restrict__ rec0,
     const float4* __restrict__ rec1, const uint2* __restrict__ foot,
     const float* __restrict__ queries, float* __restrict__ Q, float* __restrict__ T_final,
     float* __restrict__ T_save, uint32_t* __restrict__ n_contrib, const float* __restrict__ colors,
     const uint32_t* __restrict__ depth_key, float* __restrict__ rgb, float* __restrict__ depth)
 {
+    constexpr int NC = DQ / 16;  // 16-channel accumulators
     const int c = cam_of_tile(cs, tile);
     const Cam& cam = cs.c[c];
-    const int lt = tile - cam.tile_base;
-    const int tyi = lt / cam.tiles_x, txi = lt - tyi * cam.tiles_x;
-    const int px = (txi << cs.tile_shift_x) + (threadIdx.x & (cs.tile_w - 1));
-    const int py = (tyi << cs.tile_shift_y) + (threadIdx.x >> cs.tile_shift_x);
+    const Block b = wave_block(cs, cam, tile);
+    const int lane = (int)__lane_id(), l16 = lane & 15, lg = lane >> 4, half = lane >> 5;
+    const int px = b.x0 + (lane & (b.w - 1)), py = b.y0 + (lane >> b.sx);
     const bool inside = px < cam.w && py < cam.h;
     const uint2 rg = ranges[tile];
+    const uint32_t rbase = (uint32_t)c * (uint32_t)N;
 
-    float acc[DQ];
+    f32x16 acc[NC];
 #pragma unroll
-    for (int j = 0; j < DQ; ++j) acc[j] = 0.0f;
+    for (int k = 0; k < NC; ++k) acc[k] = f32x16{};
     float4 accx = make_float4(0.f, 0.f, 0.f, 0.f);
     float T = 1.0f;
     uint32_t last = 0;
-    bool done = !inside;
+    // this lane's bit of its half of the pixel mask; zero once the pixel is done
+    uint32_t bit = inside ? 1u << (lane & 31) : 0u;
     const float fpx = (float)px, fpy = (float)py;
+    const unsigned long long below = (1ull << lane) - 1ull;
 
-    // one list entry staged per thread: chunks are as long as the workgroup
-    const uint32_t chunk = blockDim.x;
-    for (uint32_t base = rg.x; base < rg.y; base += chunk) {
-        if (__syncthreads_count(done) == (int)blockDim.x) break;
-        stage_chunk<DQ, RGBD>(st, (int)(base + threadIdx.x), rg.y, c, N, tile_recs, rec0, rec1, foot,
-                              queries, colors, depth_key);
-        __syncthreads();
-        const int cnt = (int)min(chunk, rg.y - base);
-        for (int j = 0; j < cnt && !done; ++j) {
-            const uint2 f = st.fp[j];
-            if (px < (int)(f.x & 0xFFFF) || px > (int)(f.x >> 16) || py < (int)(f.y & 0xFFFF) ||
-                py > (int)(f.y >> 16))
-                continue;
-            const float4 a = st.r0[j];
-            const float4 b = st.r1[j];
-            const float dx = (a.x - fpx) + a.z;
-            const float dy = (a.y - fpy) + a.w;
-            const float power = -0.5f * (b.x * dx * dx + b.z * dy * dy) - b.y * dx * dy;
-            const float oG = b.w * __expf(power);
-            const float al = oG < kAlphaMax ? oG : kAlphaMax;
-            if (al < kAlphaMin) continue;
-            const float Tn = T * (1.0f - al);
-            if (Tn < kTStop) {
-                done = true;
-                break;
-            }
-            const float wgt = al * T;
-            const float* q = st.q + j * DQ;
+    uint32_t rnext = rg.x + lane < rg.y ? tile_recs[rg.x + lane] : 0u;
+    for (uint32_t base = rg.x; base < rg.y; base += kList) {
+        if (__ballot(bit != 0u) == 0ull) break;
+        const bool have = base + lane < rg.y;
+        const uint32_t r = rnext;
+        if (base + kList + lane < rg.y) rnext = tile_recs[base + kList + lane];
+        unsigned long long mask = 0ull;
+        Entry e{};
+        if (have) {
+            e = load_entry(r, rec0, rec1, foot);
+            mask = block_mask(b, e.fp);
+            if (mask && !block_reached(b, e.u, e.v, e.con.x, e.con.y, e.con.z, e.con.w)) mask = 0ull;
+        }
+        const unsigned long long kept = __ballot(mask != 0ull);
+        const int nk = __popcll(kept);
+        if (nk == 0) continue;
+        float z = 0.0f;  // NaN if a query of the entry is not finite
+        if (mask) {
+            const int pos = __popcll(kept & below);
+            st.ab[pos] = make_float4(e.u, e.v, e.con.x, e.con.y);
+            st.cd[pos] = make_float4(e.con.z, e.con.w, __uint_as_float(base - rg.x + lane + 1u), 0.0f);
+            st.mask[pos] = make_uint2((uint32_t)mask, (uint32_t)(mask >> 32));
+            const float4* qs = reinterpret_cast<const float4*>(queries + (size_t)(r - rbase) * DQ);
+            float4* qd = reinterpret_cast<float4*>(st.q + pos * DQ);
 #pragma unroll
-            for (int k = 0; k < DQ; ++k) acc[k] += wgt * q[k];
-            if constexpr (RGBD) {
-                const float4 x = st.x[j];
-                accx.x += wgt * x.x;
-                accx.y += wgt * x.y;
-                accx.z += wgt * x.z;
-                accx.w += wgt * x.w;
+            for (int k = 0; k < DQ / 4; ++k) {
+                const float4 v = qs[k];
+                qd[k] = v;
+                z += 0.0f * v.x + 0.0f * v.y + 0.0f * v.z + 0.0f * v.w;
             }
-            T = Tn;
-            last = base - rg.x + j + 1;
+            if constexpr (RGBD) st.x[pos] = rgbz(colors, depth_key, r, r - rbase);
+        }
+        const bool finite = __ballot(z != z) == 0ull;
+        wave_sync();
+
+        struct Item {
+            float4 a, d, x;
+            uint32_t m;
+            float q[NC];
+        };
+        auto fetch = [&](int j) {
+            Item it;
+            it.a = st.ab[j];
+            it.d = st.cd[j];
+            it.m = reinterpret_cast<const uint32_t*>(st.mask)[2 * j + half];
+#pragma unroll
+            for (int k = 0; k < NC; ++k) it.q[k] = st.q[j * DQ + 16 * k + l16];
+            if constexpr (RGBD) it.x = st.x[j];
+            return it;
+        };
+        Item nx = fetch(0);
+        for (int j = 0; j < nk; ++j) {
+            const Item it = nx;
+            nx = fetch(j + 1 < nk ? j + 1 : j);
+            const float oG = pair_og(it.a.x, it.a.y, it.a.z, it.a.w, it.d.x, it.d.y, fpx, fpy);
+            const float al = oG < kAlphaMax ? oG : kAlphaMax;
+            bool hit = (it.m & bit) != 0u && !(al < kAlphaMin);
+            const float Tn = T * (1.0f - al);
+            if (hit && Tn < kTStop) {
+                hit = false;
+                bit = 0u;
+            }
+            if (__ballot(hit) == 0ull) continue;
+            const float wgt = hit ? al * T : 0.0f;
+            T = hit ? Tn : T;
+            last = hit ? __float_as_uint(it.d.z) : last;
+            if (finite) {
+#pragma unroll
+                for (int k = 0; k < NC; ++k)
+                    acc[k] = __builtin_amdgcn_mfma_f32_16x16x1f32(wgt, it.q[k], acc[k], 0, 0, 0);
+            } else {
+                // a query that is not finite reaches only the pixels it is
+                // blended into (0 x inf would reach the whole block)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float wp = __shfl(wgt, 16 * (i >> 2) + 4 * lg + (i & 3), kWave);
+#pragma unroll
+                    for (int k = 0; k < NC; ++k) acc[k][i] = wp != 0.0f ? fmaf(wp, it.q[k], acc[k][i]) : acc[k][i];
+                }
+            }
+            if constexpr (RGBD) {
+                if (hit) {
+                    accx.x += wgt * it.x.x;
+                    accx.y += wgt * it.x.y;
+                    accx.z += wgt * it.x.z;
+                    accx.w += wgt * it.x.w;
+                }
+            }
+        }
+        wave_sync();
+    }
+    // accumulator register 4 j + i holds pixel 16 j + 4 (lane / 16) + i, channel lane % 16
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int p = 16 * (i >> 2) + 4 * lg + (i & 3);
+        const int qx = b.x0 + (p & (b.w - 1)), qy = b.y0 + (p >> b.sx);
+        if (qx < cam.w && qy < cam.h) {
+            float* qo = Q + ((size_t)cam.pix_base + (size_t)qy * cam.w + qx) * DQ + l16;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) qo[16 * k] = acc[k][i];
         }
     }
     if (inside) {
         const size_t p = (size_t)cam.pix_base + (size_t)py * cam.w + px;
-        float4* qo = reinterpret_cast<float4*>(Q + p * DQ);
-#pragma unroll
-        for (int k = 0; k < DQ / 4; ++k)
-            qo[k] = make_float4(acc[4 * k], acc[4 * k + 1], acc[4 * k + 2], acc[4 * k + 3]);
         T_final[p] = T;
         T_save[p] = T;
         n_contrib[p] = last;
@@ -440,7 +600,8 @@ __global__ __launch_bounds__(256) void k_raster_fwd(
     uint32_t* __restrict__ queue, const float* __restrict__ colors,
     const uint32_t* __restrict__ depth_key, float* __restrict__ rgb, float* __restrict__ depth)
 {
-    __shared__ TileStage<DQ, RGBD> st;
+    extern __shared__ __align__(16) char smem[];  // one stage per wave
+    FwdStage<DQ, RGBD>& st = reinterpret_cast<FwdStage<DQ, RGBD>*>(smem)[threadIdx.x / kWave];
     if (!PERSIST) {
         raster_fwd_tile<DQ, RGBD>(st, blockIdx.x, cs, N, ranges, tile_recs, rec0, rec1, foot, queries, Q,
                                   T_final, T_save, n_contrib, colors, depth_key, rgb, depth);
@@ -448,7 +609,7 @@ __global__ __launch_bounds__(256) void k_raster_fwd(
     }
     __shared__ int s_tile;
     for (;;) {
-        __syncthreads();  // the previous tile is done with the staged lists
+        __syncthreads();  // every wave has read the last tile index
         if (threadIdx.x == 0) s_tile = (int)atomicAdd(queue, 1u);
         __syncthreads();
         const int tile = __builtin_amdgcn_readfirstlane(s_tile);
@@ -460,75 +621,87 @@ __global__ __launch_bounds__(256) void k_raster_fwd(
 
 // ------------------------------------------------------------- raster bwd
 
-// The partner's copy of x in a halving step with lane mask M (1, 2, 4 or 8),
-// through DPP inside a 16-lane row: lane ^ 1 and lane ^ 2 by quad permutes,
-// lane ^ 8 by rotating the row by 8, and for M = 4 the mirror lane within the
-// 8-lane half row (7 - i), whose M bit is also the opposite one.  A partner
-// that differs in bits below M too is as good as lane ^ M: those bits are
-// combined at the later steps all the same.
-template <int M>
-__device__ inline float partner(float x)
+constexpr int kBatch = 16;  // entries whose sums one set of matrix products forms
+
+// A wave's queue of entries to visit (what a list step leaves plus fewer than
+// kBatch from before) and its exchange buffers: weights w and dL/d(power) dp
+// of a batch as [pixel][16 entries], and the batch's screen-space gradients.
+// slot(p, e): four entries of a pixel are one 16-byte chunk, and a pixel's four
+// chunks are permuted by its position so that the chunk writes (lane = pixel)
+// and the word reads (lane = entry) both cover all banks.
+struct BwdStage {
+    float4 ab[kBatch + kList];    // u, v, A, B
+    float4 cd[kBatch + kList];    // C, opacity, list position, record
+    uint2 mask[kBatch + kList];   // the block's pixels inside the footprint
+    float w[kWave * kBatch];
+    float dp[kWave * kBatch];
+    float grad[kBatch * 8];
+    static __device__ int chunk(int p, int q) { return p * kBatch + 4 * ((q ^ (p >> 1)) & 3); }
+    static __device__ int slot(int p, int e) { return chunk(p, e >> 2) + (e & 3); }
+};
+
+// Mean over the 16 lanes of a group, in every lane; zero if it is not finite.
+__device__ inline float mean16(float x)
 {
-    constexpr int ctrl = M == 1 ? 0xB1 : M == 2 ? 0x4E : M == 4 ? 0x141 : 0x128;
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), ctrl, 0xF, 0xF, false));
+    x += dpp_f<0xB1, 0xF, 0xF, false>(x);   // lane ^ 1
+    x += dpp_f<0x4E, 0xF, 0xF, false>(x);   // lane ^ 2
+    x += dpp_f<0x141, 0xF, 0xF, false>(x);  // the mirror lane of the half row
+    x += dpp_f<0x140, 0xF, 0xF, false>(x);  // the mirror lane of the row
+    x *= 1.0f / 16.0f;
+    return fabsf(x) <= 3.4e38f ? x : 0.0f;
 }
 
-// Transposed wave reduction of N values: at the step with lane mask M a lane
-// keeps the upper half of its values if its M bit is set, the lower half
-// otherwise, and adds the partner's copy of the half it keeps.  For M = 32 and
-// 16 one v_permlane32_swap / v_permlane16_swap of the pair (v[k], v[k + H])
-// leaves, in every lane, its own kept value and the partner's copy of it in the
-// two results (the swap trades the upper lanes of the first operand for the
-// lower lanes of the second), so their sum is the step; the smaller masks use
-// DPP.  No LDS traffic either way.
-template <int N, int M>
-__device__ inline void halving_sum(float* v, unsigned lane)
+// Four 16-lane groups by four registers, transposed: register j of lane group
+// g becomes register g of lane group j.
+__device__ inline void transpose_groups(float& a, float& b, float& c, float& d)
 {
-    if constexpr (N > 1 && M >= 1) {
-        constexpr int H = N / 2;
-        if constexpr (M == 32 || M == 16) {
-#pragma unroll
-            for (int k = 0; k < H; ++k) {
-                const auto r = M == 32 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(v[k]),
-                                                                          __float_as_uint(v[k + H]), false, false)
-                                       : __builtin_amdgcn_permlane16_swap(__float_as_uint(v[k]),
-                                                                          __float_as_uint(v[k + H]), false, false);
-                v[k] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-            }
-        } else {
-            const bool upper = (lane & M) != 0;
-#pragma unroll
-            for (int k = 0; k < H; ++k) {
-                const float send = upper ? v[k] : v[k + H];
-                const float keep = upper ? v[k + H] : v[k];
-                v[k] = keep + partner<M>(send);
-            }
-        }
-        halving_sum<H, M / 2>(v, lane);
-    }
+    auto swap32 = [](float& x, float& y) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        x = __uint_as_float(r[0]);
+        y = __uint_as_float(r[1]);
+    };
+    auto swap16 = [](float& x, float& y) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        x = __uint_as_float(r[0]);
+        y = __uint_as_float(r[1]);
+    };
+    swap32(a, c);
+    swap32(b, d);
+    swap16(a, b);
+    swap16(c, d);
 }
 
-// Wave sum of N values (N a power of two, 8 <= N <= 64): the halving steps
-// over the masks 32 ... 64 / N, then the lanes that still differ in the lower
-// mask bits add their partners' totals.  Afterwards the lanes whose low
-// 6 - log2(N) bits are zero hold value lane >> (6 - log2(N)).
-template <int N>
-__device__ inline float wave_sum_split(float* v, unsigned lane)
+// Sum over the four 16-lane groups, in every lane.
+__device__ inline float sum_groups(float x)
 {
-    static_assert(N >= 8 && N <= 64 && (N & (N - 1)) == 0, "N must be a power of two in [8, 64]");
-    constexpr int S = N == 8 ? 3 : N == 16 ? 2 : N == 32 ? 1 : 0;
-    halving_sum<N, 32>(v, lane);
-    if constexpr (S >= 3) v[0] += partner<4>(v[0]);
-    if constexpr (S >= 2) v[0] += partner<2>(v[0]);
-    if constexpr (S >= 1) v[0] += partner<1>(v[0]);
-    return v[0];
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
 }
 
 // rec_grad[r] = (du, dv, dA, dB, dC, dopacity) accumulated over pixels; with
 // RGBD also d_colors[g] and rec_dz[r] (the gradient of the record's depth).
+//
+// A pixel walks its list back to front, rebuilding the transmittance by
+// division.  With s_j = q_j . dQ the gradient of alpha_j is T_j (s_j - b_j),
+// where b_j, the blend of the s behind entry j, follows b <- b + alpha (s - b):
+// one scalar per pixel in place of a blended query.  Batches of 16 entries:
+//   s      [16 entries x 64 pixels] = q dQ^T by MFMA (K = channels), then a
+//          transposition of lane groups puts one pixel on each lane;
+//   walk   per entry and pixel: alpha, T, w = alpha T, dp = dL/d(power);
+//   sums   through LDS (lane = pixel to lane = entry, a quarter of the pixels):
+//          d_queries [16 x DQ] = w^T dQ by MFMA (K = pixels), and the sums of
+//          dp (1, dx, dy, dx^2, dx dy, dy^2) that the six screen-space
+//          gradients need by vector operations (as moments about the block's
+//          centre they would also be a product, but small Gaussians away from
+//          the centre then lose digits to cancellation).
+// Per entry and wave about 35 vector operations and 64 + 2 DQ MFMA cycles;
+// summed over lanes and channels by vector operations it was about 180 at
+// DQ = 16 and 250 at DQ = 32.
 template <int DQ, bool RGBD>
 __device__ inline void raster_bwd_tile(
-    TileStage<DQ, RGBD>& st, uint32_t& s_max, const int tile, const CamSet& cs, int N,
+    BwdStage& st, const int tile, const CamSet& cs, int N,
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ tile_recs,
     const float4* __restrict__ rec0, const float4* __restrict__ rec1,
     const uint2* __restrict__ foot, const float* __restrict__ queries,
@@ -538,166 +711,322 @@ __device__ inline void raster_bwd_tile(
     const float* __restrict__ d_rgb, const float* __restrict__ d_depth, float* __restrict__ d_colors,
     float* __restrict__ rec_dz)
 {
+    constexpr int NC = DQ / 16;  // 16-channel column blocks
+    constexpr int KD = DQ / 4;   // channels per lane group in the dot products
+    constexpr int KX = KD + (RGBD ? 1 : 0);
     const int c = cam_of_tile(cs, tile);
     const Cam& cam = cs.c[c];
-    const int lt = tile - cam.tile_base;
-    const int tyi = lt / cam.tiles_x, txi = lt - tyi * cam.tiles_x;
-    const int px = (txi << cs.tile_shift_x) + (threadIdx.x & (cs.tile_w - 1));
-    const int py = (tyi << cs.tile_shift_y) + (threadIdx.x >> cs.tile_shift_x);
+    const Block b = wave_block(cs, cam, tile);
+    const int lane = (int)__lane_id(), l16 = lane & 15, lg = lane >> 4, half = lane >> 5;
+    const int px = b.x0 + (lane & (b.w - 1)), py = b.y0 + (lane >> b.sx);
     const bool inside = px < cam.w && py < cam.h;
     const uint2 rg = ranges[tile];
-    const unsigned lane = __lane_id();
+    const uint32_t rbase = (uint32_t)c * (uint32_t)N;
+    // pixel of the block -> row of the pixel arrays, or -1 outside the image
+    auto row_of = [&](int p) -> long long {
+        const int x = b.x0 + (p & (b.w - 1)), y = b.y0 + (p >> b.sx);
+        return x < cam.w && y < cam.h ? cam.pix_base + (long long)y * cam.w + x : -1ll;
+    };
+    const long long prow = row_of(lane);
+    float T = inside ? T_final[prow] : 1.0f;
+    const uint32_t last = inside ? n_contrib[prow] : 0u;
+    int maxlast = (int)last;
+    for (int o = 32; o >= 1; o >>= 1) maxlast = max(maxlast, __shfl_xor(maxlast, o, kWave));
+    if (maxlast == 0) return;
 
-    float g[DQ], behind[DQ];
-    float4 gx = make_float4(0.f, 0.f, 0.f, 0.f), behindx = gx;
-    float T = 1.0f;
-    uint32_t last = 0;
-    if (inside) {
-        const size_t p = (size_t)cam.pix_base + (size_t)py * cam.w + px;
-        if constexpr (RGBD) gx = make_float4(d_rgb[3 * p], d_rgb[3 * p + 1], d_rgb[3 * p + 2], d_depth[p]);
-        const float4* gi = reinterpret_cast<const float4*>(dQ + p * DQ);
+    // dQ as the B operand of the dot products (K = channels: lane group lg
+    // holds channels KD lg .. + KD - 1 of pixel 16 j + l16) and of the sums
+    // over the pixels (step s: lane group lg holds pixel 4 s + lg, lane l16 a channel)
+    float gd[4][KD], gs[NC][16], gdx[RGBD ? 4 : 1], gsx[RGBD ? 16 : 1];
+    float z = 0.0f;
 #pragma unroll
-        for (int k = 0; k < DQ / 4; ++k) {
-            const float4 v = gi[k];
-            g[4 * k] = v.x; g[4 * k + 1] = v.y; g[4 * k + 2] = v.z; g[4 * k + 3] = v.w;
+    for (int j = 0; j < 4; ++j) {
+        const long long p = row_of(16 * j + l16);
+#pragma unroll
+        for (int k = 0; k < KD; k += 4) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (p >= 0) v = *reinterpret_cast<const float4*>(dQ + p * DQ + KD * lg + k);
+            gd[j][k] = v.x; gd[j][k + 1] = v.y; gd[j][k + 2] = v.z; gd[j][k + 3] = v.w;
+            z += 0.0f * v.x + 0.0f * v.y + 0.0f * v.z + 0.0f * v.w;
         }
-        T = T_final[p];
-        last = n_contrib[p];
-    } else {
-#pragma unroll
-        for (int k = 0; k < DQ; ++k) g[k] = 0.0f;
+        if constexpr (RGBD) {
+            gdx[j] = p < 0 ? 0.0f : lg < 3 ? d_rgb[3 * p + lg] : d_depth[p];
+            z += 0.0f * gdx[j];
+        }
     }
 #pragma unroll
-    for (int k = 0; k < DQ; ++k) behind[k] = 0.0f;
-    if (threadIdx.x == 0) s_max = 0;
-    __syncthreads();
-    atomicMax(&s_max, last);
-    __syncthreads();
-    const uint32_t maxlast = s_max;
+    for (int s = 0; s < 16; ++s) {
+        const int q = 4 * s + lg;
+        const long long p = row_of(q);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) gs[k][s] = p >= 0 ? dQ[p * DQ + 16 * k + l16] : 0.0f;
+        if constexpr (RGBD) gsx[s] = p < 0 || l16 > 3 ? 0.0f : l16 < 3 ? d_rgb[3 * p + l16] : d_depth[p];
+    }
+    // A pixel whose upstream gradient is not finite reaches only the entries
+    // blended into it: its column of the pixel sums is cleared (0 x inf would
+    // reach every entry of the batch) and its terms are added one by one.
+    unsigned long long bad = 0ull;
+    if (__ballot(z != 0.0f) != 0ull) {
+        float y = 0.0f;
+        if (inside) {
+            #pragma unroll 1
+            for (int k = 0; k < DQ; ++k) y += 0.0f * dQ[prow * DQ + k];
+            if constexpr (RGBD) y += 0.0f * d_rgb[3 * prow] + 0.0f * d_rgb[3 * prow + 1] + 0.0f * d_rgb[3 * prow + 2] + 0.0f * d_depth[prow];
+        }
+        bad = __ballot(y != 0.0f);
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            if (!((bad >> (4 * s + lg)) & 1ull)) continue;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) gs[k][s] = 0.0f;
+            if constexpr (RGBD) gsx[s] = 0.0f;
+        }
+    }
+    const bool mine_bad = ((bad >> lane) & 1ull) != 0ull;
+    const uint32_t bit = 1u << (lane & 31);
     const float fpx = (float)px, fpy = (float)py;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    float behind = 0.0f;
 
-    const int chunk = (int)blockDim.x;  // one staged entry per thread
-    for (int end = (int)maxlast; end > 0; end -= chunk) {
-        const int start = end > chunk ? end - chunk : 0;
-        __syncthreads();
-        stage_chunk<DQ, RGBD>(st, (int)(rg.x + start + threadIdx.x), rg.x + end, c, N, tile_recs, rec0,
-                              rec1, foot, queries, colors, depth_key);
-        __syncthreads();
-        for (int j = end - 1; j >= start; --j) {
-            const int sj = j - start;
-            float gu = 0.f, gv = 0.f, gA = 0.f, gB = 0.f, gC = 0.f, gO = 0.f, wq = 0.f;
-            bool hit = false;
-            if ((uint32_t)j < last) {
-                const uint2 f = st.fp[sj];
-                if (px >= (int)(f.x & 0xFFFF) && px <= (int)(f.x >> 16) &&
-                    py >= (int)(f.y & 0xFFFF) && py <= (int)(f.y >> 16)) {
-                    const float4 a = st.r0[sj];
-                    const float4 b = st.r1[sj];
-                    const float dx = (a.x - fpx) + a.z;
-                    const float dy = (a.y - fpy) + a.w;
-                    const float power = -0.5f * (b.x * dx * dx + b.z * dy * dy) - b.y * dx * dy;
-                    const float G = __expf(power);
-                    const float oG = b.w * G;
-                    const float al = oG < kAlphaMax ? oG : kAlphaMax;
-                    if (al >= kAlphaMin) {
-                        hit = true;
-                        // 1 - al >= 0.01: the hardware reciprocal (1 ulp) replaces the
-                        // IEEE division sequence
-                        T = T * __builtin_amdgcn_rcpf(1.0f - al);
-                        wq = al * T;
-                        const float* q = st.q + sj * DQ;
-                        // B <- al q + (1 - al) B as B + al (q - B), the difference
-                        // shared with the alpha gradient: three operations a channel
-                        float dal = 0.0f;
+    // s[e] = value of entry e (rows; lane group lg holds its channels KD lg ..)
+    // times dQ of this lane's pixel
+    auto dots = [&](const float* q, float* sv) {
+        f32x4 s4[4];
 #pragma unroll
-                        for (int k = 0; k < DQ; ++k) {
-                            const float df = q[k] - behind[k];
-                            dal += df * g[k];
-                            behind[k] += al * df;
-                        }
-                        if constexpr (RGBD) {
-                            const float4 x = st.x[sj];
-                            const float d0 = x.x - behindx.x, d1 = x.y - behindx.y;
-                            const float d2 = x.z - behindx.z, d3 = x.w - behindx.w;
-                            dal += d0 * gx.x + d1 * gx.y + d2 * gx.z + d3 * gx.w;
-                            behindx.x += al * d0;
-                            behindx.y += al * d1;
-                            behindx.z += al * d2;
-                            behindx.w += al * d3;
-                        }
-                        dal *= T;
-                        if (oG < kAlphaMax) {
-                            const float dp = dal * oG;
-                            gu = -dp * (b.x * dx + b.y * dy);
-                            gv = -dp * (b.z * dy + b.y * dx);
-                            gA = -0.5f * dp * dx * dx;
-                            gB = -dp * dx * dy;
-                            gC = -0.5f * dp * dy * dy;
-                            gO = dal * G;
-                        }
-                    }
+        for (int j = 0; j < 4; ++j) {
+            s4[j] = f32x4{};
+#pragma unroll
+            for (int k = 0; k < KD; ++k) s4[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(q[k], gd[j][k], s4[j], 0, 0, 0);
+            if constexpr (RGBD) s4[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(q[KD], gdx[j], s4[j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float t0 = s4[0][i], t1 = s4[1][i], t2 = s4[2][i], t3 = s4[3][i];
+            transpose_groups(t0, t1, t2, t3);
+            sv[i] = t0; sv[4 + i] = t1; sv[8 + i] = t2; sv[12 + i] = t3;
+        }
+    };
+    // The dot products are taken with q - qref, qref the mean query of the
+    // wave's first batch: where the queries share an offset, s - b would lose
+    // the digits of it.  With rref = qref . dQ and past = the product of
+    // (1 - alpha) of the entries behind, s - b = (s' - b') + rref past.
+    bool have_ref = false;
+    float qref[KX], rref = 0.0f, past = 1.0f;
+
+    auto batch = [&](int q0) {  // queue entries q0 .. q0 + 15
+        // the queries of entry l16, channels KD lg ..; in flight during the alphas
+        const uint32_t er = __float_as_uint(st.cd[q0 + l16].w);
+        const float* qrow = queries + (size_t)(er - rbase) * DQ + KD * lg;
+        float qv[KX];
+#pragma unroll
+        for (int k = 0; k < KD; k += 4) {
+            const float4 v = *reinterpret_cast<const float4*>(qrow + k);
+            qv[k] = v.x; qv[k + 1] = v.y; qv[k + 2] = v.z; qv[k + 3] = v.w;
+        }
+        if constexpr (RGBD) qv[KD] = lg < 3 ? colors[3 * (size_t)(er - rbase) + lg] : __uint_as_float(depth_key[er]);
+        float og[kBatch];  // o G where the pair counts, else 0
+#pragma unroll
+        for (int e = 0; e < kBatch; ++e) {
+            const float4 a = st.ab[q0 + e], d = st.cd[q0 + e];
+            const uint32_t m = reinterpret_cast<const uint32_t*>(st.mask)[2 * (q0 + e) + half];
+            const float oG = pair_og(a.x, a.y, a.z, a.w, d.x, d.y, fpx, fpy);
+            const float al = oG < kAlphaMax ? oG : kAlphaMax;
+            const bool hit = (m & bit) != 0u && __float_as_uint(d.z) < last && al >= kAlphaMin;
+            og[e] = hit ? oG : 0.0f;
+            if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four entries' LDS reads in flight, not sixteen
+        }
+        if (!have_ref) {  // the wave's first batch: its mean query, and the pixels' dot products with it
+            have_ref = true;
+            float sv[kBatch];
+#pragma unroll
+            for (int k = 0; k < KD; ++k) qref[k] = mean16(qv[k]);
+            if constexpr (RGBD) qref[KD] = mean16(qv[KD]);
+            dots(qref, sv);
+            rref = sv[0];
+        }
+#pragma unroll
+        for (int k = 0; k < KX; ++k) qv[k] -= qref[k];
+        float sv[kBatch];  // s of entry e for this lane's pixel
+        dots(qv, sv);
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+            float w4[4], p4[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = 4 * e4 + i;
+                const bool hit = og[e] != 0.0f;
+                const float al = og[e] < kAlphaMax ? og[e] : kAlphaMax;
+                // 1 - al >= 0.01: the hardware reciprocal (1 ulp) replaces the
+                // IEEE division sequence; 1 where the pair does not count
+                const float om = 1.0f - al;
+                T = T * __builtin_amdgcn_rcpf(om);
+                w4[i] = al * T;
+                const float t = hit ? sv[e] - behind : 0.0f;
+                behind += al * t;
+                p4[i] = hit && og[e] < kAlphaMax ? fmaf(rref, past, t) * T * og[e] : 0.0f;
+                past *= om;
+            }
+            *reinterpret_cast<float4*>(st.w + BwdStage::chunk(lane, e4)) = make_float4(w4[0], w4[1], w4[2], w4[3]);
+            *reinterpret_cast<float4*>(st.dp + BwdStage::chunk(lane, e4)) = make_float4(p4[0], p4[1], p4[2], p4[3]);
+        }
+        wave_sync();
+        if (mine_bad) {
+#pragma unroll 1
+            for (int e = 0; e < kBatch; ++e) {
+                const float w = st.w[BwdStage::slot(lane, e)];
+                if (w == 0.0f) continue;
+                const uint32_t r = __float_as_uint(st.cd[q0 + e].w);
+                const size_t g = (size_t)(r - rbase);
+#pragma unroll 1
+                for (int k = 0; k < DQ; ++k) unsafeAtomicAdd(d_queries + g * DQ + k, w * dQ[prow * DQ + k]);
+                if constexpr (RGBD) {
+                    for (int k = 0; k < 3; ++k) unsafeAtomicAdd(d_colors + g * 3 + k, w * d_rgb[3 * prow + k]);
+                    unsafeAtomicAdd(rec_dz + r, w * d_depth[prow]);
                 }
             }
-            if (__ballot(hit) == 0ull) continue;
-            if constexpr (!RGBD) {
-                // The DQ query terms and the 6 screen-space terms (padded to 8)
-                // summed over the wave as two sets, each by halving (no padding
-                // of the query set to 32 or 64 values): lane l then holds query
-                // term l >> (6 - log2 DQ) and screen term l >> 3.
-                float vq[DQ], vs[8] = {gu, gv, gA, gB, gC, gO, 0.0f, 0.0f};
+        }
+        // from here a lane is entry l16 and the pixels 4 s + lg
+        f32x4 dq4[NC], dx4 = {};
 #pragma unroll
-                for (int k = 0; k < DQ; ++k) vq[k] = wq * g[k];
-                const float sq = wave_sum_split<DQ>(vq, lane);
-                const float ss = wave_sum_split<8>(vs, lane);
-                constexpr int SQ = DQ == 16 ? 2 : 1;
-                const bool oq = (lane & ((1u << SQ) - 1u)) == 0 && sq != 0.0f;
-                const bool os = (lane & 7u) == 0 && (lane >> 3) < 6 && ss != 0.0f;
-                if (oq || os) {
-                    const uint32_t r = st.rec[sj];
-                    if (oq) unsafeAtomicAdd(d_queries + (size_t)(r - (uint32_t)c * (uint32_t)N) * DQ + (lane >> SQ), sq);
-                    if (os) unsafeAtomicAdd(rec_grad + (size_t)r * 6 + (lane >> 3), ss);
-                }
-                continue;
+        for (int k = 0; k < NC; ++k) dq4[k] = f32x4{};
+        float da[16];
+        // slot(4 s + lg, l16): two bases, 128 words further for every other s
+        const float *we = st.w + BwdStage::slot(lg, l16), *wo = st.w + BwdStage::slot(4 + lg, l16);
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            const float* at = (s & 1 ? wo : we) + 128 * (s >> 1);
+            const float wa = at[0];
+            da[s] = at[kWave * kBatch];  // st.dp
+#pragma unroll
+            for (int k = 0; k < NC; ++k) dq4[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa, gs[k][s], dq4[k], 0, 0, 0);
+            if constexpr (RGBD) dx4 = __builtin_amdgcn_mfma_f32_16x16x4f32(wa, gsx[s], dx4, 0, 0, 0);
+        }
+        // sums of dp (1, dx, dy, dx^2, dx dy, dy^2) over the lane's pixels,
+        // each product formed from the pair's own offsets
+        const float4 ea = st.ab[q0 + l16], ed = st.cd[q0 + l16];
+        float m0 = 0.f, sx = 0.f, sy = 0.f, sxx = 0.f, sxy = 0.f, syy = 0.f;
+        if (b.sx == 3) {
+            // 8 x 8: pixels 8 y + lg and 8 y + 4 + lg of row y, summed by rows first
+            const float xa = ea.x - (float)(b.x0 + lg), xb = ea.x - (float)(b.x0 + 4 + lg);
+            const float xa2 = xa * xa, xb2 = xb * xb;
+#pragma unroll
+            for (int y = 0; y < 8; ++y) {
+                const float dy = ea.y - (float)(b.y0 + y);
+                const float r0 = da[2 * y] + da[2 * y + 1];
+                const float r1 = da[2 * y] * xa + da[2 * y + 1] * xb;
+                m0 += r0;
+                sx += r1;
+                sxx += da[2 * y] * xa2 + da[2 * y + 1] * xb2;
+                const float t = r0 * dy;
+                sy += t;
+                syy += t * dy;
+                sxy += r1 * dy;
             }
-            // With RGBD: 6 screen-space terms, DQ query terms, 3 colour terms
-            // and the depth term, padded to NV, summed over the wave by halving:
-            // at each step a lane keeps half of its values and adds the partner's
-            // copy of that half, so after log2(64) steps lane l holds the total of
-            // value (l >> 1) (NV = 32) or l (NV = 64).
-            constexpr int NX = RGBD ? 4 : 0;
-            constexpr int NT = 6 + DQ + NX;
-            constexpr int NV = (NT <= 32) ? 32 : 64;
-            float v[NV];
-            v[0] = gu; v[1] = gv; v[2] = gA; v[3] = gB; v[4] = gC; v[5] = gO;
+        } else {
+            int lq = lg;
+            asm volatile("" : "+v"(lq));  // the 16 pixel positions are formed here, not kept across the batches
 #pragma unroll
-            for (int k = 0; k < DQ; ++k) v[6 + k] = wq * g[k];
+            for (int s = 0; s < 16; ++s) {
+                const int q = 4 * s + lq;
+                const float dx = ea.x - (float)(b.x0 + (q & (b.w - 1))), dy = ea.y - (float)(b.y0 + (q >> b.sx));
+                const float tx = da[s] * dx, ty = da[s] * dy;
+                m0 += da[s];
+                sx += tx;
+                sy += ty;
+                sxx += tx * dx;
+                sxy += tx * dy;
+                syy += ty * dy;
+            }
+        }
+        m0 = sum_groups(m0); sx = sum_groups(sx); sy = sum_groups(sy);
+        sxx = sum_groups(sxx); sxy = sum_groups(sxy); syy = sum_groups(syy);
+        if (lane < kBatch) {
+            *reinterpret_cast<float4*>(st.grad + 8 * lane) =
+                make_float4(-(ea.z * sx + ea.w * sy), -(ed.x * sy + ea.w * sx), -0.5f * sxx, -sxy);
+            *reinterpret_cast<float2*>(st.grad + 8 * lane + 4) =
+                make_float2(-0.5f * syy, m0 != 0.0f ? m0 / ed.y : 0.0f);
+        }
+        // result register i of lane group lg is entry 4 lg + i, column l16
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t r = __float_as_uint(st.cd[q0 + 4 * lg + i].w);
+            const size_t g = (size_t)(r - rbase);
+#pragma unroll
+            for (int k = 0; k < NC; ++k)
+                if (dq4[k][i] != 0.0f) unsafeAtomicAdd(d_queries + g * DQ + 16 * k + l16, dq4[k][i]);
             if constexpr (RGBD) {
-                v[6 + DQ] = wq * gx.x;
-                v[7 + DQ] = wq * gx.y;
-                v[8 + DQ] = wq * gx.z;
-                v[9 + DQ] = wq * gx.w;
+                if (l16 < 4 && dx4[i] != 0.0f) unsafeAtomicAdd(l16 < 3 ? d_colors + g * 3 + l16 : rec_dz + r, dx4[i]);
             }
+        }
+        wave_sync();
 #pragma unroll
-            for (int k = NT; k < NV; ++k) v[k] = 0.0f;
-            halving_sum<NV, 32>(v, lane);
-            if (NV == 32) v[0] += partner<1>(v[0]);
-            const int idx = NV == 32 ? (int)(lane >> 1) : (int)lane;
-            const bool owner = (NV == 64 || (lane & 1) == 0) && idx < NT && v[0] != 0.0f;
-            if (owner) {
-                const uint32_t r = st.rec[sj];
-                const size_t gi = (size_t)(r - (uint32_t)c * (uint32_t)N);
-                float* dst = idx < 6 ? rec_grad + (size_t)r * 6 + idx
-                           : idx < 6 + DQ ? d_queries + gi * DQ + (idx - 6)
-                           : idx < 9 + DQ ? d_colors + gi * 3 + (idx - 6 - DQ)
-                                          : rec_dz + r;
-                unsafeAtomicAdd(dst, v[0]);
+        for (int i = 0; i < 2; ++i) {
+            const int e = 8 * i + (lane >> 3), t = lane & 7;
+            const float v = st.grad[8 * e + t];
+            if (t < 6 && v != 0.0f)
+                unsafeAtomicAdd(rec_grad + (size_t)__float_as_uint(st.cd[q0 + e].w) * 6 + t, v);
+        }
+        wave_sync();
+    };
+
+    int nq = 0;  // entries in the queue
+    int pos0 = maxlast - 1 - lane;
+    uint32_t rnext = pos0 >= 0 ? tile_recs[rg.x + pos0] : 0u;
+    for (int end = maxlast; end > 0; end -= kList) {
+        const int j = end - 1 - lane;  // back to front
+        const uint32_t r = rnext;
+        if (j - kList >= 0) rnext = tile_recs[rg.x + j - kList];
+        unsigned long long mask = 0ull;
+        Entry e{};
+        if (j >= 0) {
+            e = load_entry(r, rec0, rec1, foot);
+            mask = block_mask(b, e.fp);
+            if (mask && !block_reached(b, e.u, e.v, e.con.x, e.con.y, e.con.z, e.con.w)) mask = 0ull;
+        }
+        const unsigned long long kept = __ballot(mask != 0ull);
+        if (mask) {
+            const int pos = nq + __popcll(kept & below);
+            st.ab[pos] = make_float4(e.u, e.v, e.con.x, e.con.y);
+            st.cd[pos] = make_float4(e.con.z, e.con.w, __uint_as_float((uint32_t)j), __uint_as_float(r));
+            st.mask[pos] = make_uint2((uint32_t)mask, (uint32_t)(mask >> 32));
+        }
+        nq += __popcll(kept);
+        if (end <= kList && (nq & (kBatch - 1)) != 0) {
+            // the last list step: fill the last batch with entries of no pixel
+            const int pad = kBatch - (nq & (kBatch - 1));
+            if (lane < pad) {
+                st.ab[nq + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+                st.cd[nq + lane] = make_float4(0.f, 1.f, 0.f, __uint_as_float(rbase));
+                st.mask[nq + lane] = make_uint2(0u, 0u);
             }
+            nq += pad;
+        }
+        wave_sync();
+        int q0 = 0;
+        for (; q0 + kBatch <= nq; q0 += kBatch) batch(q0);
+        // what is left moves to the front (fewer than kBatch entries)
+        nq -= q0;
+        if (q0 > 0 && nq > 0) {
+            float4 ta, td;
+            uint2 tm;
+            if (lane < nq) {
+                ta = st.ab[q0 + lane];
+                td = st.cd[q0 + lane];
+                tm = st.mask[q0 + lane];
+            }
+            wave_sync();
+            if (lane < nq) {
+                st.ab[lane] = ta;
+                st.cd[lane] = td;
+                st.mask[lane] = tm;
+            }
+            wave_sync();
         }
     }
 }
 
 template <int DQ, bool PERSIST, bool RGBD>
-__global__ __launch_bounds__(256) void k_raster_bwd(
+__global__ __launch_bounds__(256, DQ == 16 && !RGBD ? 3 : 2) void k_raster_bwd(
     CamSet cs, int N, const uint2* __restrict__ ranges, const uint32_t* __restrict__ tile_recs,
     const float4* __restrict__ rec0, const float4* __restrict__ rec1,
     const uint2* __restrict__ foot, const float* __restrict__ queries,
@@ -707,10 +1036,10 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
     const uint32_t* __restrict__ depth_key, const float* __restrict__ d_rgb,
     const float* __restrict__ d_depth, float* __restrict__ d_colors, float* __restrict__ rec_dz)
 {
-    __shared__ TileStage<DQ, RGBD> st;
-    __shared__ uint32_t s_max;
+    extern __shared__ __align__(16) char smem[];  // one stage per wave
+    BwdStage& st = reinterpret_cast<BwdStage*>(smem)[threadIdx.x / kWave];
     if (!PERSIST) {
-        raster_bwd_tile<DQ, RGBD>(st, s_max, blockIdx.x, cs, N, ranges, tile_recs, rec0, rec1, foot, queries,
+        raster_bwd_tile<DQ, RGBD>(st, blockIdx.x, cs, N, ranges, tile_recs, rec0, rec1, foot, queries,
                                   T_final, n_contrib, dQ, rec_grad, d_queries, colors, depth_key, d_rgb,
                                   d_depth, d_colors, rec_dz);
         return;
@@ -722,7 +1051,7 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
         __syncthreads();
         const int tile = __builtin_amdgcn_readfirstlane(s_tile);
         if (tile >= cs.total_tiles) break;
-        raster_bwd_tile<DQ, RGBD>(st, s_max, tile, cs, N, ranges, tile_recs, rec0, rec1, foot, queries,
+        raster_bwd_tile<DQ, RGBD>(st, tile, cs, N, ranges, tile_recs, rec0, rec1, foot, queries,
                                   T_final, n_contrib, dQ, rec_grad, d_queries, colors, depth_key, d_rgb,
                                   d_depth, d_colors, rec_dz);
     }
@@ -937,10 +1266,13 @@ hipError_t render_forward_launch(lam_ctx* ctx, const RenderArgs& A, const Render
                          : (A.d == 16 ? (pers ? k_raster_fwd<16, true, false> : k_raster_fwd<16, false, false>)
                                       : (pers ? k_raster_fwd<32, true, false> : k_raster_fwd<32, false, false>));
         int grid = cs.total_tiles;
+        const size_t stage = A.d == 16 ? (rgbd ? sizeof(FwdStage<16, true>) : sizeof(FwdStage<16, false>))
+                                       : (rgbd ? sizeof(FwdStage<32, true>) : sizeof(FwdStage<32, false>));
+        const size_t lds = stage * (threads / kWave);
         if (pers)  // its work counter, counters[2], was cleared with the sort scratch
-            grid = std::min(grid, ctx_resident_blocks(ctx, (const void*)kern, threads));
+            grid = std::min(grid, ctx_resident_blocks(ctx, (const void*)kern, threads, lds));
         ProfScope ps(ctx, "raster_fwd", st);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, cs, A.n, (const uint2*)L.ranges,
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, st, cs, A.n, (const uint2*)L.ranges,
                            trecs, (const float4*)L.rec0, (const float4*)L.rec1, (const uint2*)L.foot,
                            A.queries, A.Q, A.T_final, L.t_final, L.n_contrib, L.counters + 2, A.colors,
                            (const uint32_t*)L.depth_key, A.rgb, A.depth);
@@ -971,13 +1303,14 @@ hipError_t render_backward_launch(lam_ctx* ctx, const RenderArgs& A, const Rende
                          : (A.d == 16 ? (pers ? k_raster_bwd<16, true, false> : k_raster_bwd<16, false, false>)
                                       : (pers ? k_raster_bwd<32, true, false> : k_raster_bwd<32, false, false>));
         int grid = cs.total_tiles;
+        const size_t lds = sizeof(BwdStage) * (threads / kWave);
         if (pers) {
             e = launch_fill_u32(L.counters + 3, 1, 0u, st);
             if (e != hipSuccess) return e;
-            grid = std::min(grid, ctx_resident_blocks(ctx, (const void*)kern, threads));
+            grid = std::min(grid, ctx_resident_blocks(ctx, (const void*)kern, threads, lds));
         }
         ProfScope ps(ctx, "raster_bwd", st);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, cs, A.n, (const uint2*)L.ranges,
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, st, cs, A.n, (const uint2*)L.ranges,
                            trecs, (const float4*)L.rec0, (const float4*)L.rec1, (const uint2*)L.foot,
                            A.queries, (const float*)L.t_final, (const uint32_t*)L.n_contrib, A.dQ,
                            L.rec_grad, A.d_queries, L.counters + 3, A.colors, (const uint32_t*)L.depth_key,
