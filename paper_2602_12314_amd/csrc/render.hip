@@ -307,14 +307,17 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ key
 // products q . dQ and the sums over the pixels as K = 4 products.  With one
 // lane per pixel and the channels in registers, the same sums read every
 // channel of every entry through LDS broadcasts (8 cycles of the CU's one LDS
-// pipe per 16 bytes and wave, so the forward was bound by LDS: 106 us at
-// 640x480, 333 us for the 2M-Gaussian keyframe) and the backward spent some
-// 180 of its 250 vector operations per entry on channels and wave sums.
+// pipe per 16 bytes and wave) and the backward spent most of its vector
+// operations per entry on channels and wave sums.  Measured, before -> now:
+// forward 106 -> 48 us and backward 256 -> 118 us at 640x480 with 100k
+// Gaussians (d = 16), 333 -> 150 us and 830 -> 402 us at 1200x680 with 2M
+// (d = 32).
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kList = 64;  // list entries taken at a time, one per lane
+constexpr int kGroup = 4;  // entries left of them that the forward visits at a time
 
 // The wave's block of the tile: x0, y0 its first pixel, width 1 << sx.
 // rows has the bit of each row's first pixel.
@@ -431,15 +434,18 @@ __device__ inline float4 rgbz(const float* __restrict__ colors, const uint32_t* 
 // weights (Eq. 2: colour; depth by the same alpha blending).
 template <int DQ, bool RGBD>
 struct FwdStage {
-    float4 ab[kList];
-    float4 cd[kList];
-    uint2 mask[kList];
-    float q[kList * DQ];
-    float4 x[RGBD ? kList : 1];
+    float4 ab[kList + kGroup];
+    float4 cd[kList + kGroup];
+    uint2 mask[kList + kGroup];
+    float q[(kList + kGroup) * DQ];
+    float4 x[RGBD ? kList + kGroup : 1];
 };
 
-// Per entry and wave the VALU takes some 25 operations (mask, alpha, T) and the
-// matrix cores 32 cycles per 16 channels, beside it.  The K = 1 product adds
+// Bound by vector issue: per entry and wave some 25 operations (mask, alpha, T),
+// and 32 matrix cycles per 16 channels beside them.  Four entries are visited
+// without a branch between them: one at a time, with a branch past entries that
+// hit nothing, the register copies at each merge and the serial latency of the
+// alphas made it 71 us at 640x480 instead of 48.  The K = 1 product adds
 // w q to each channel by one fused multiply-add per entry, in list order, so
 // Q is what a chain of them per pixel gives.
 template <int DQ, bool RGBD>
@@ -469,26 +475,31 @@ __device__ inline void raster_fwd_tile(
     uint32_t last = 0;
     // this lane's bit of its half of the pixel mask; zero once the pixel is done
     uint32_t bit = inside ? 1u << (lane & 31) : 0u;
-    const float fpx = (float)px, fpy = (float)py;
+    float fpx = (float)px, fpy = (float)py;
+    asm volatile("" : "+v"(fpx), "+v"(fpy));  // held as floats, not converted again at each entry
     const unsigned long long below = (1ull << lane) - 1ull;
 
-    uint32_t rnext = rg.x + lane < rg.y ? tile_recs[rg.x + lane] : 0u;
+    // list entries and record ids are requested a step and two steps ahead
+    Entry en{};
+    if (rg.x + lane < rg.y) en = load_entry(tile_recs[rg.x + lane], rec0, rec1, foot);
+    uint32_t rnext = rg.x + kList + lane < rg.y ? tile_recs[rg.x + kList + lane] : 0u;
     for (uint32_t base = rg.x; base < rg.y; base += kList) {
         if (__ballot(bit != 0u) == 0ull) break;
-        const bool have = base + lane < rg.y;
-        const uint32_t r = rnext;
-        if (base + kList + lane < rg.y) rnext = tile_recs[base + kList + lane];
+        const Entry e = en;
+        const uint32_t r = e.rec;
         unsigned long long mask = 0ull;
-        Entry e{};
-        if (have) {
-            e = load_entry(r, rec0, rec1, foot);
+        if (base + lane < rg.y) {
             mask = block_mask(b, e.fp);
             if (mask && !block_reached(b, e.u, e.v, e.con.x, e.con.y, e.con.z, e.con.w)) mask = 0ull;
+        }
+        if (base + kList + lane < rg.y) {
+            en = load_entry(rnext, rec0, rec1, foot);
+            if (base + 2 * kList + lane < rg.y) rnext = tile_recs[base + 2 * kList + lane];
         }
         const unsigned long long kept = __ballot(mask != 0ull);
         const int nk = __popcll(kept);
         if (nk == 0) continue;
-        float z = 0.0f;  // NaN if a query of the entry is not finite
+        float z = 0.0f;  // NaN if a value of the entry is not finite
         if (mask) {
             const int pos = __popcll(kept & below);
             st.ab[pos] = make_float4(e.u, e.v, e.con.x, e.con.y);
@@ -502,62 +513,89 @@ __device__ inline void raster_fwd_tile(
                 qd[k] = v;
                 z += 0.0f * v.x + 0.0f * v.y + 0.0f * v.z + 0.0f * v.w;
             }
-            if constexpr (RGBD) st.x[pos] = rgbz(colors, depth_key, r, r - rbase);
+            if constexpr (RGBD) {
+                const float4 x = rgbz(colors, depth_key, r, r - rbase);
+                st.x[pos] = x;
+                z += 0.0f * x.x + 0.0f * x.y + 0.0f * x.z;
+            }
+        }
+        if (lane < kGroup - 1) {  // fills the last group with entries of no pixel
+            st.mask[nk + lane] = make_uint2(0u, 0u);
+#pragma unroll
+            for (int k = 0; k < DQ / 4; ++k)
+                reinterpret_cast<float4*>(st.q + (nk + lane) * DQ)[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (RGBD) st.x[nk + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
         const bool finite = __ballot(z != z) == 0ull;
         wave_sync();
 
-        struct Item {
-            float4 a, d, x;
-            uint32_t m;
-            float q[NC];
-        };
-        auto fetch = [&](int j) {
-            Item it;
-            it.a = st.ab[j];
-            it.d = st.cd[j];
-            it.m = reinterpret_cast<const uint32_t*>(st.mask)[2 * j + half];
-#pragma unroll
-            for (int k = 0; k < NC; ++k) it.q[k] = st.q[j * DQ + 16 * k + l16];
-            if constexpr (RGBD) it.x = st.x[j];
-            return it;
-        };
-        Item nx = fetch(0);
-        for (int j = 0; j < nk; ++j) {
-            const Item it = nx;
-            nx = fetch(j + 1 < nk ? j + 1 : j);
-            const float oG = pair_og(it.a.x, it.a.y, it.a.z, it.a.w, it.d.x, it.d.y, fpx, fpy);
+        // one entry's step: its weight per pixel (zero where it does not count)
+        auto step = [&](float oG, uint32_t m, float pos1) {
             const float al = oG < kAlphaMax ? oG : kAlphaMax;
-            bool hit = (it.m & bit) != 0u && !(al < kAlphaMin);
+            const bool in = (m & bit) != 0u && !(al < kAlphaMin);
             const float Tn = T * (1.0f - al);
-            if (hit && Tn < kTStop) {
-                hit = false;
-                bit = 0u;
-            }
-            if (__ballot(hit) == 0ull) continue;
+            const bool stop = in && Tn < kTStop, hit = in && !stop;
+            bit = stop ? 0u : bit;
             const float wgt = hit ? al * T : 0.0f;
             T = hit ? Tn : T;
-            last = hit ? __float_as_uint(it.d.z) : last;
-            if (finite) {
+            last = hit ? __float_as_uint(pos1) : last;
+            return wgt;
+        };
+        if (finite) {
+            // kGroup entries at a time and no branch in between: their alphas do
+            // not wait for each other, the transmittance then takes them in order
+            for (int j0 = 0; j0 < nk; j0 += kGroup) {
+                float og[kGroup], pos1[kGroup], qv[kGroup][NC];
+                uint32_t mk[kGroup];
 #pragma unroll
-                for (int k = 0; k < NC; ++k)
-                    acc[k] = __builtin_amdgcn_mfma_f32_16x16x1f32(wgt, it.q[k], acc[k], 0, 0, 0);
-            } else {
-                // a query that is not finite reaches only the pixels it is
-                // blended into (0 x inf would reach the whole block)
+                for (int i = 0; i < kGroup; ++i) {
+                    const float4 a = st.ab[j0 + i];
+                    const float4 d = st.cd[j0 + i];
+                    mk[i] = reinterpret_cast<const uint32_t*>(st.mask)[2 * (j0 + i) + half];
+                    pos1[i] = d.z;
+#pragma unroll
+                    for (int k = 0; k < NC; ++k) qv[i][k] = st.q[(j0 + i) * DQ + 16 * k + l16];
+                    og[i] = pair_og(a.x, a.y, a.z, a.w, d.x, d.y, fpx, fpy);
+                }
+#pragma unroll
+                for (int i = 0; i < kGroup; ++i) {
+                    const float wgt = step(og[i], mk[i], pos1[i]);
+#pragma unroll
+                    for (int k = 0; k < NC; ++k)
+                        acc[k] = __builtin_amdgcn_mfma_f32_16x16x1f32(wgt, qv[i][k], acc[k], 0, 0, 0);
+                    if constexpr (RGBD) {
+                        const float4 x = st.x[j0 + i];
+                        accx.x += wgt * x.x;
+                        accx.y += wgt * x.y;
+                        accx.z += wgt * x.z;
+                        accx.w += wgt * x.w;
+                    }
+                }
+                if (__ballot(bit != 0u) == 0ull) break;
+            }
+        } else {
+            // a value that is not finite reaches only the pixels it is blended
+            // into (in the product, 0 x inf would reach the whole block)
+#pragma unroll 1
+            for (int j = 0; j < nk; ++j) {
+                const float4 a = st.ab[j], d = st.cd[j];
+                const uint32_t m = reinterpret_cast<const uint32_t*>(st.mask)[2 * j + half];
+                const float wgt = step(pair_og(a.x, a.y, a.z, a.w, d.x, d.y, fpx, fpy), m, d.z);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const float wp = __shfl(wgt, 16 * (i >> 2) + 4 * lg + (i & 3), kWave);
 #pragma unroll
-                    for (int k = 0; k < NC; ++k) acc[k][i] = wp != 0.0f ? fmaf(wp, it.q[k], acc[k][i]) : acc[k][i];
+                    for (int k = 0; k < NC; ++k)
+                        acc[k][i] = wp != 0.0f ? fmaf(wp, st.q[j * DQ + 16 * k + l16], acc[k][i]) : acc[k][i];
                 }
-            }
-            if constexpr (RGBD) {
-                if (hit) {
-                    accx.x += wgt * it.x.x;
-                    accx.y += wgt * it.x.y;
-                    accx.z += wgt * it.x.z;
-                    accx.w += wgt * it.x.w;
+                if constexpr (RGBD) {
+                    const float4 x = st.x[j];
+                    if (wgt != 0.0f) {
+                        accx.x += wgt * x.x;
+                        accx.y += wgt * x.y;
+                        accx.z += wgt * x.z;
+                        accx.w += wgt * x.w;
+                    }
                 }
             }
         }
@@ -696,9 +734,10 @@ __device__ inline float sum_groups(float x)
 //          gradients need by vector operations (as moments about the block's
 //          centre they would also be a product, but small Gaussians away from
 //          the centre then lose digits to cancellation).
-// Per entry and wave about 35 vector operations and 64 + 2 DQ MFMA cycles;
-// summed over lanes and channels by vector operations it was about 180 at
-// DQ = 16 and 250 at DQ = 32.
+// Per entry and wave about 45 vector operations and 4 DQ MFMA cycles.  What is
+// left of its time at 640x480 (118 us): 22 us are the prologue and the list
+// steps, 26 us the atomics (32 cache lines of them per batch), the rest the
+// walk at two to three waves per SIMD.
 template <int DQ, bool RGBD>
 __device__ inline void raster_bwd_tile(
     BwdStage& st, const int tile, const CamSet& cs, int N,
@@ -730,10 +769,6 @@ __device__ inline void raster_bwd_tile(
     const long long prow = row_of(lane);
     float T = inside ? T_final[prow] : 1.0f;
     const uint32_t last = inside ? n_contrib[prow] : 0u;
-    int maxlast = (int)last;
-    for (int o = 32; o >= 1; o >>= 1) maxlast = max(maxlast, __shfl_xor(maxlast, o, kWave));
-    if (maxlast == 0) return;
-
     // dQ as the B operand of the dot products (K = channels: lane group lg
     // holds channels KD lg .. + KD - 1 of pixel 16 j + l16) and of the sums
     // over the pixels (step s: lane group lg holds pixel 4 s + lg, lane l16 a channel)
@@ -762,6 +797,10 @@ __device__ inline void raster_bwd_tile(
         for (int k = 0; k < NC; ++k) gs[k][s] = p >= 0 ? dQ[p * DQ + 16 * k + l16] : 0.0f;
         if constexpr (RGBD) gsx[s] = p < 0 || l16 > 3 ? 0.0f : l16 < 3 ? d_rgb[3 * p + l16] : d_depth[p];
     }
+    int maxlast = (int)last;
+    for (int o = 32; o >= 1; o >>= 1) maxlast = max(maxlast, __shfl_xor(maxlast, o, kWave));
+
+    if (maxlast == 0) return;
     // A pixel whose upstream gradient is not finite reaches only the entries
     // blended into it: its column of the pixel sums is cleared (0 x inf would
     // reach every entry of the batch) and its terms are added one by one.
@@ -784,7 +823,8 @@ __device__ inline void raster_bwd_tile(
     }
     const bool mine_bad = ((bad >> lane) & 1ull) != 0ull;
     const uint32_t bit = 1u << (lane & 31);
-    const float fpx = (float)px, fpy = (float)py;
+    float fpx = (float)px, fpy = (float)py;
+    asm volatile("" : "+v"(fpx), "+v"(fpy));
     const unsigned long long below = (1ull << lane) - 1ull;
     float behind = 0.0f;
 
@@ -813,6 +853,31 @@ __device__ inline void raster_bwd_tile(
     bool have_ref = false;
     float qref[KX], rref = 0.0f, past = 1.0f;
 
+    // The sums of a batch are added to memory once the next batch's queries are
+    // requested: memory operations complete in order, so a load issued after
+    // the atomics would wait for them.
+    bool pending = false;
+    f32x4 pq[NC], pxz = {};
+    uint32_t pr[4], pgr[2];
+    float pg[2];
+    auto flush = [&]() {
+        if (!pending) return;
+        // result register i of lane group lg is entry 4 lg + i, column l16
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const size_t g = (size_t)(pr[i] - rbase);
+#pragma unroll
+            for (int k = 0; k < NC; ++k)
+                if (pq[k][i] != 0.0f) unsafeAtomicAdd(d_queries + g * DQ + 16 * k + l16, pq[k][i]);
+            if constexpr (RGBD) {
+                if (l16 < 4 && pxz[i] != 0.0f) unsafeAtomicAdd(l16 < 3 ? d_colors + g * 3 + l16 : rec_dz + pr[i], pxz[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if ((lane & 7) < 6 && pg[i] != 0.0f) unsafeAtomicAdd(rec_grad + (size_t)pgr[i] * 6 + (lane & 7), pg[i]);
+    };
+
     auto batch = [&](int q0) {  // queue entries q0 .. q0 + 15
         // the queries of entry l16, channels KD lg ..; in flight during the alphas
         const uint32_t er = __float_as_uint(st.cd[q0 + l16].w);
@@ -824,6 +889,9 @@ __device__ inline void raster_bwd_tile(
             qv[k] = v.x; qv[k + 1] = v.y; qv[k + 2] = v.z; qv[k + 3] = v.w;
         }
         if constexpr (RGBD) qv[KD] = lg < 3 ? colors[3 * (size_t)(er - rbase) + lg] : __uint_as_float(depth_key[er]);
+        __builtin_amdgcn_sched_barrier(0);
+        flush();
+        __builtin_amdgcn_sched_barrier(0);
         float og[kBatch];  // o G where the pair counts, else 0
 #pragma unroll
         for (int e = 0; e < kBatch; ++e) {
@@ -831,9 +899,12 @@ __device__ inline void raster_bwd_tile(
             const uint32_t m = reinterpret_cast<const uint32_t*>(st.mask)[2 * (q0 + e) + half];
             const float oG = pair_og(a.x, a.y, a.z, a.w, d.x, d.y, fpx, fpy);
             const float al = oG < kAlphaMax ? oG : kAlphaMax;
-            const bool hit = (m & bit) != 0u && __float_as_uint(d.z) < last && al >= kAlphaMin;
+            const bool hit = ((m & bit) != 0u) & (__float_as_uint(d.z) < last) & (al >= kAlphaMin);
             og[e] = hit ? oG : 0.0f;
-            if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four entries' LDS reads in flight, not sixteen
+            // formed here, four entries' LDS reads in flight (sunk to its use it
+            // would keep the operands of all sixteen in registers)
+            asm volatile("" : "+v"(og[e]));
+            if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
         if (!have_ref) {  // the wave's first batch: its mean query, and the pixels' dot products with it
             have_ref = true;
@@ -861,9 +932,10 @@ __device__ inline void raster_bwd_tile(
                 const float om = 1.0f - al;
                 T = T * __builtin_amdgcn_rcpf(om);
                 w4[i] = al * T;
-                const float t = hit ? sv[e] - behind : 0.0f;
+                const float d0 = sv[e] - behind, t = hit ? d0 : 0.0f;
                 behind += al * t;
-                p4[i] = hit && og[e] < kAlphaMax ? fmaf(rref, past, t) * T * og[e] : 0.0f;
+                const float f = fmaf(rref, past, t) * T * og[e];
+                p4[i] = (hit & (og[e] < kAlphaMax)) ? f : 0.0f;
                 past *= om;
             }
             *reinterpret_cast<float4*>(st.w + BwdStage::chunk(lane, e4)) = make_float4(w4[0], w4[1], w4[2], w4[3]);
@@ -946,42 +1018,40 @@ __device__ inline void raster_bwd_tile(
             *reinterpret_cast<float2*>(st.grad + 8 * lane + 4) =
                 make_float2(-0.5f * syy, m0 != 0.0f ? m0 / ed.y : 0.0f);
         }
-        // result register i of lane group lg is entry 4 lg + i, column l16
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t r = __float_as_uint(st.cd[q0 + 4 * lg + i].w);
-            const size_t g = (size_t)(r - rbase);
-#pragma unroll
-            for (int k = 0; k < NC; ++k)
-                if (dq4[k][i] != 0.0f) unsafeAtomicAdd(d_queries + g * DQ + 16 * k + l16, dq4[k][i]);
-            if constexpr (RGBD) {
-                if (l16 < 4 && dx4[i] != 0.0f) unsafeAtomicAdd(l16 < 3 ? d_colors + g * 3 + l16 : rec_dz + r, dx4[i]);
-            }
-        }
         wave_sync();
 #pragma unroll
+        for (int k = 0; k < NC; ++k) pq[k] = dq4[k];
+        if constexpr (RGBD) pxz = dx4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pr[i] = __float_as_uint(st.cd[q0 + 4 * lg + i].w);
+#pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const int e = 8 * i + (lane >> 3), t = lane & 7;
-            const float v = st.grad[8 * e + t];
-            if (t < 6 && v != 0.0f)
-                unsafeAtomicAdd(rec_grad + (size_t)__float_as_uint(st.cd[q0 + e].w) * 6 + t, v);
+            const int e = 8 * i + (lane >> 3);
+            pg[i] = st.grad[8 * e + (lane & 7)];
+            pgr[i] = __float_as_uint(st.cd[q0 + e].w);
         }
+        pending = true;
         wave_sync();
     };
 
     int nq = 0;  // entries in the queue
-    int pos0 = maxlast - 1 - lane;
-    uint32_t rnext = pos0 >= 0 ? tile_recs[rg.x + pos0] : 0u;
+    // list entries and record ids are requested a step and two steps ahead
+    const int jl = maxlast - 1 - lane;  // back to front
+    Entry en{};
+    if (jl >= 0) en = load_entry(tile_recs[rg.x + jl], rec0, rec1, foot);
+    uint32_t rnext = jl - kList >= 0 ? tile_recs[rg.x + jl - kList] : 0u;
     for (int end = maxlast; end > 0; end -= kList) {
-        const int j = end - 1 - lane;  // back to front
-        const uint32_t r = rnext;
-        if (j - kList >= 0) rnext = tile_recs[rg.x + j - kList];
+        const int j = end - 1 - lane;
+        const Entry e = en;
+        const uint32_t r = e.rec;
         unsigned long long mask = 0ull;
-        Entry e{};
         if (j >= 0) {
-            e = load_entry(r, rec0, rec1, foot);
             mask = block_mask(b, e.fp);
             if (mask && !block_reached(b, e.u, e.v, e.con.x, e.con.y, e.con.z, e.con.w)) mask = 0ull;
+        }
+        if (j - kList >= 0) {
+            en = load_entry(rnext, rec0, rec1, foot);
+            if (j - 2 * kList >= 0) rnext = tile_recs[rg.x + j - 2 * kList];
         }
         const unsigned long long kept = __ballot(mask != 0ull);
         if (mask) {
@@ -1023,6 +1093,7 @@ __device__ inline void raster_bwd_tile(
             wave_sync();
         }
     }
+    flush();
 }
 
 template <int DQ, bool PERSIST, bool RGBD>
