@@ -19,6 +19,7 @@
 // (k_dec_dv), which rebuilds P~ from Q, K and the saved row max rather than
 // reading it.  The softmax is recomputed in the backward part, never stored.
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -134,10 +135,7 @@ constexpr int kScLd = 40;
 // pixels (16 bytes in BF16) per store: chunk q = q0, q0 + dq, ... covers row
 // q / 4, pixels 8 (q % 4) .. + 7.  This turns the one-pixel-per-lane MFMA
 // result layout into whole-chunk stores of the pixel-blocked transposes.
-// With PERM the pixels of each 16-pixel half are stored in perm16 order
-// (position p holds pixel perm16(p)), the order in which k_dec_dv's recomputed
-// P~ fragments hold them.
-template <class P, bool PERM = false>
+template <class P>
 __device__ inline void store_transposed(const typename P::T* S, int ld, int nrows, typename P::T* Dst,
                                         int q0, int dq)
 {
@@ -145,11 +143,26 @@ __device__ inline void store_transposed(const typename P::T* S, int ld, int nrow
         const int row = q >> 2, pg = (q & 3) * 8;
         typename P::Frag f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int pix = PERM ? (pg & 16) + perm16((pg & 15) + j) : pg + j;
-            f[j] = S[pix * ld + row];
-        }
+        for (int j = 0; j < 8; ++j) f[j] = S[(pg + j) * ld + row];
         *reinterpret_cast<typename P::Frag*>(Dst + (size_t)row * kPx + pg) = f;
+    }
+}
+
+// The same tile as k_dec_dv's operands: per 32 rows and 16-pixel half k one
+// fragment of 64 lanes x 8 elements (lane 32 h + row % 32), a contiguous run
+// for the wave that loads it, its pixels in perm16 order (position 8 h + j
+// holds pixel perm16(8 h + j)), the order in which k_dec_dv's recomputed P~
+// fragments hold them.
+template <class P>
+__device__ inline void store_pixel_frags(const typename P::T* S, int ld, int ntiles, typename P::T* Dst, int lane)
+{
+    const int col = lane & 31, h = lane >> 5;
+    for (int i = 0; i < 2 * ntiles; ++i) {
+        const int row = 32 * (i >> 1) + col, k = i & 1;
+        typename P::Frag f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) f[j] = S[(16 * k + 8 * (j >> 2) + 4 * h + (j & 3)) * ld + row];
+        *reinterpret_cast<typename P::Frag*>(Dst + (size_t)(i * kWave + lane) * 8) = f;
     }
 }
 
@@ -283,9 +296,10 @@ struct RowsArgs {
     const float* sv_fold;   // FP8 forward: s^V_j * 448 / max_j s^V_j   [Mp]
     const float* fp8_unscale;  // FP8 forward: max_j s^V_j / 448         [1]
     float* M2;  // [blocks, 32]      row max of the logits in log2 units, per pixel
-    void* Gt;   // [blocks, D, 32]   G^T
+    void* Gt;   // [blocks, D/32, 2, 64 lanes, 8]  G^T as k_dec_dv's fragments
     void* St;   // [blocks, Mp, 32]  dS^T
     void* Qt;   // [blocks, 32, 32]  Q^T (rows >= d zero)
+    void* Qb;   // [blocks, d/16, 64 lanes, 8]  Q in the fragment-major layout (zero past n)
 };
 
 // Chunks of fragments kept in flight by the contraction loops (a ring of
@@ -375,11 +389,16 @@ __global__ __launch_bounds__(NW * kWave) void k_dec_rows(RowsArgs a)
             }
     };
     load_qf();
-    // Q^T of 32-pixel block g for the dK reduction, written by wave g (rows >= d zero)
+    // written by wave g for its 32-pixel block: the query fragments for k_dec_dv,
+    // Q^T for the dK reduction (rows >= d zero)
     if (MODE != MODE_INFER) {
 #pragma unroll
         for (int g = 0; g < NPG; ++g) {
             if (w != g) continue;
+#pragma unroll
+            for (int c = 0; c < NQ; ++c)
+                *reinterpret_cast<Frag*>(reinterpret_cast<T*>(a.Qb) + ((((size_t)(blk * NPG + g) * NQ + c) << 6) + lane) * 8) =
+                    qf[g][c];
             T* qt = reinterpret_cast<T*>(a.Qt) + (size_t)(blk * NPG + g) * 32 * kPx;
 #pragma unroll
             for (int c = 0; c < NQ; ++c)
@@ -873,12 +892,11 @@ __global__ __launch_bounds__(NW * kWave) void k_dec_rows(RowsArgs a)
         for (int ww = 0; ww < NW; ++ww) s += rslot(3, ww, g)[col];
         delta[g] = s;
     }
-    // G^T of this wave's D rows from the LDS copy, in whole chunks, pixels in the
-    // perm16 order of k_dec_dv's P~ fragments
+    // G^T of this wave's D rows from the LDS copy, as k_dec_dv's fragments
 #pragma unroll
     for (int g = 0; g < NPG; ++g) {
         T* Gt = reinterpret_cast<T*>(a.Gt) + ((size_t)(blk * NPG + g) * a.D + 32 * w * NT) * kPx;
-        store_transposed<P, true>(X + g * kPx * ldg + 32 * w * NT, ldg, 32 * NT, Gt, lane, kWave);
+        store_pixel_frags<P>(X + g * kPx * ldg + 32 * w * NT, ldg, NT, Gt, lane);
     }
 
     // ---- per atom tile: dP = G V^T, dS = P~ (dP - delta) / sqrt(d), dQ^T += K^T dS^T
@@ -1098,26 +1116,26 @@ __global__ __launch_bounds__(256) void k_dec_tn(const void* At_, int rowsA, cons
                 out[(size_t)(i0 + 32 * a + crow(r, h)) * rowsB + j0 + 32 * q + col] = c[a][q][r];
 }
 
-// dV partials with P~ rebuilt instead of read: C_part[split][i][j] = sum over
-// the split's 32-pixel blocks of P~[px][i] G[px][j].  Per block the wave's two
-// atom tiles of S = Q K^T come from MFMA with the pixel as the row, so a lane
-// holds one atom and 16 pixels (rows crow(r, h)); P~ = exp2(S log2(e)/sqrt(d)
-// - m2[px]) with the row max k_dec_rows saved, and result registers 8k..8k+7
-// are directly the A fragment of pixel chunk k in perm16 order, the order in
-// which k_dec_rows stores G^T.  Waves 2 x 2, each 64 atoms x 64 features; two
-// blocks of Q, m2 and G^T fragments in flight; splits mapped as in k_dec_tn.
-// dV split-K GEMM.  A workgroup owns 128 atoms x 128 QT feature columns and a
-// range of pixel blocks.  Per block, wave w rebuilds P~ for atom tile w only
-// (S = Q K^T with the pixel as the MFMA row, so each lane holds one atom and
-// 16 pixels in perm16 order, then exp2 against the saved row max) and leaves
-// it in LDS as the A fragments of the dV product; after one barrier every
-// wave multiplies all four atom tiles by the G^T fragments of its own 32 QT
-// columns.  P~ is thus computed once per (atom, pixel) and feature-column
-// tile, and the LDS slots alternate between blocks so one barrier per block
-// suffices (a wave can write slot b + 1 while a slower one still reads slot b,
-// and cannot reach slot b + 2 before that wave has passed the barrier of b + 1).
+// dV split-K GEMM: C_part[split][i][j] = sum over the split's 32-pixel blocks
+// of P~[px][i] G[px][j], with P~ rebuilt instead of read.  A workgroup owns 128
+// atoms x 128 QT feature columns and a range of pixel blocks.  Per block, wave
+// w rebuilds P~ for atom tile w only (S = Q K^T with the pixel as the MFMA row,
+// so each lane holds one atom and 16 pixels in perm16 order, the order in which
+// k_dec_rows stores G^T; then exp2 against the row max k_dec_rows saved) and
+// leaves it in LDS as the A fragments of the dV product; every wave multiplies
+// all four atom tiles by the G^T fragments of its own 32 QT columns.
+//
+// Bound by the matrix cores if the rebuild runs beside them: a step issues the
+// products of block b, a quarter of them at a time, and between the quarters
+// the exponentials of block b + 1, whose fragments go to the other LDS slot.
+// One barrier per block: a slot is rewritten one barrier after its last read.
+// With the rebuild of a block before its own products the matrix cores idled
+// through it (29 % busy): 2.52 ms at 816000 x 1024 x 1024, 1.44 ms at 816000 x
+// 512 x 768, 115 us at 307200 x 256 x 512; now 1.73, 0.74 and 0.108 ms.  All
+// operands are read as whole fragments (1 KB runs); requesting their lines
+// further ahead costs more requests than it hides latency (1.76 -> 2.00 ms).
 template <class P, int DQ, int QT>
-__global__ __launch_bounds__(256, P::kBytes == 2 ? 2 : 1) void k_dec_dv(const float* __restrict__ Q, int n, const void* Kb_, int M,
+__global__ __launch_bounds__(256, P::kBytes == 2 ? 2 : 1) void k_dec_dv(const void* Qb_, const void* Kb_,
                                                 const float* __restrict__ m2, float scale_log2, const void* Gt_,
                                                 int Mp, int D, int nblocks, int splits, int tiles_i, int tiles_j,
                                                 float* __restrict__ part)
@@ -1126,6 +1144,8 @@ __global__ __launch_bounds__(256, P::kBytes == 2 ? 2 : 1) void k_dec_dv(const fl
     using Frag = typename P::Frag;
     constexpr int NQ = DQ / 16;
     __shared__ __align__(32) T pf[2][4][2][kWave * 8];
+    __shared__ __align__(16) float mrow[4][kPx];  // each wave's row maxima of the block it rebuilds
+    const T* Qb = reinterpret_cast<const T*>(Qb_);
     const T* Kb = reinterpret_cast<const T*>(Kb_);
     const T* Gt = reinterpret_cast<const T*>(Gt_);
     const int ntiles = tiles_i * tiles_j;
@@ -1145,7 +1165,6 @@ __global__ __launch_bounds__(256, P::kBytes == 2 ? 2 : 1) void k_dec_dv(const fl
     const int b0 = split * per, b1 = min(nblocks, b0 + per);
 
     Frag kf[NQ];
-    const bool atom_ok = mine_ok && i0 + 32 * w + col < M;
 #pragma unroll
     for (int c = 0; c < NQ; ++c) kf[c] = load_frag<P>(Kb, mine_ok ? i0 / 32 + w : 0, c, NQ, lane);
     f32x16 acc[4][QT];
@@ -1154,78 +1173,117 @@ __global__ __launch_bounds__(256, P::kBytes == 2 ? 2 : 1) void k_dec_dv(const fl
 #pragma unroll
         for (int q = 0; q < QT; ++q) acc[t][q] = f32x16{};
 
-    // one block's operands, requested a block ahead: the Q fragments of pixel
-    // col (converted when their loads land; zero past n), the row max of pixel
-    // col (the lane's 16 pixels take theirs by lane shuffles when used), and
-    // the G^T fragments of this wave's columns.  Holding the converted
-    // fragments and one row max per lane instead of the float rows and 16 row
-    // maxima keeps the kernel within two waves per SIMD.
-    struct Blk {
+    // operands of the rebuild of one block: its Q fragments as k_dec_rows left
+    // them (zero past n) and the row max of pixel col
+    struct Qm {
         Frag q[NQ];
         float m;
+    };
+    struct Gf {
         Frag g[QT][2];
     };
-    auto load = [&](int blk, Blk& B) {
-        const int px = blk * kPx + col;
-        const bool valid = px < n;
-        const float* qrow = Q + (size_t)(valid ? px : n - 1) * DQ;
+    auto load_q = [&](int blk, Qm& B) {
 #pragma unroll
-        for (int c = 0; c < NQ; ++c) {
-            const float4 x0 = *reinterpret_cast<const float4*>(qrow + 16 * c + 8 * h);
-            const float4 x1 = *reinterpret_cast<const float4*>(qrow + 16 * c + 8 * h + 4);
-            const float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-            float z[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) z[e] = valid ? v[e] : 0.0f;
-            B.q[c] = P::from_f32(z);
-        }
+        for (int c = 0; c < NQ; ++c) B.q[c] = load_frag<P>(Qb, blk, c, NQ, lane);
         B.m = m2[(size_t)blk * kPx + col];
+    };
+    auto load_g = [&](int blk, Gf& B) {
 #pragma unroll
         for (int q = 0; q < QT; ++q)
 #pragma unroll
             for (int k = 0; k < 2; ++k)
-                B.g[q][k] = P::load(Gt + ((size_t)blk * D + j0 + 32 * q + col) * kPx + 16 * k + 8 * h);
+                B.g[q][k] = P::load(Gt + ((size_t)blk * D + j0 + 32 * q) * kPx + (k * kWave + lane) * 8);
     };
-    auto compute = [&](int blk, const Blk& B) {
+    float* ms = mrow[w];
+    // result registers 4 r4 .. + 3 of a lane are pixels 8 r4 + 4 h ..
+    auto rowmax4 = [&](int r4) { return *reinterpret_cast<const float4*>(ms + 8 * r4 + 4 * h); };
+    auto afrag = [&](int slot, int t, int k) { return *reinterpret_cast<const Frag*>(&pf[slot][t][k][lane * 8]); };
+    auto put = [&](int slot, int k, const float* p) {
+        *reinterpret_cast<Frag*>(&pf[slot][w][k][lane * 8]) = P::from_f32(p + 8 * k);
+    };
+    auto logits = [&](const Qm& B) {
+        f32x16 s = {};
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) P::mma(s, B.q[c], kf[c]);
+        return s;
+    };
+    // Block blk's products (its fragments in slot blk & 1), and between them
+    // block blk + 1's rebuild: the order below is kept as written, so that the
+    // exponentials issue while the products run.  P~ of a padded atom is
+    // whatever its zero row gives; its result rows are never read back.
+    auto step = [&](int blk, const Gf& G, const Qm& next, auto&& request, auto full) {
         const int slot = blk & 1;
-        {
-            f32x16 sacc = {};
-#pragma unroll
-            for (int c = 0; c < NQ; ++c) P::mma(sacc, B.q[c], kf[c]);
-            float p[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float mr = __shfl(B.m, crow(r, h), kWave);  // row max of the pixel in row crow(r, h)
-                p[r] = atom_ok ? exp2_weight(sacc[r] * scale_log2 - mr) : 0.0f;
-            }
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-                *reinterpret_cast<Frag*>(&pf[slot][w][k][lane * 8]) = P::from_f32(p + 8 * k);
-        }
-        __syncthreads();
+        if (h == 0) ms[col] = next.m;
+        request();  // the operands of the next step
+        const f32x16 s = logits(next);
+        Frag a0 = afrag(slot, 0, 0), a1 = afrag(slot, 0, 1);
+        float4 mr = rowmax4(0);
+        float p[16];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            if (t < ntv) {
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const Frag af = *reinterpret_cast<const Frag*>(&pf[slot][t][k][lane * 8]);
-#pragma unroll
-                    for (int q = 0; q < QT; ++q) P::mma(acc[t][q], af, B.g[q][k]);
-                }
+            const float mm[4] = {mr.x, mr.y, mr.z, mr.w};
+            Frag n0, n1;
+            if (t < 3) {
+                n0 = afrag(slot, t + 1, 0);
+                n1 = afrag(slot, t + 1, 1);
+                mr = rowmax4(t + 1);
             }
+            int r = 0;
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int q = 0; q < QT; ++q) {
+                    if (decltype(full)::value || t < ntv) P::mma(acc[t][q], k == 0 ? a0 : a1, G.g[q][k]);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int e = 0; e < 2 / QT; ++e, ++r) {
+                        p[4 * t + r] = exp2_weight(s[4 * t + r] * scale_log2 - mm[r]);
+                        asm volatile("" : "+v"(p[4 * t + r]));  // here, not where it is packed
+                    }
+                    if (t == 1 && k == 1 && q == QT - 1) put(slot ^ 1, 0, p);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            a0 = n0;
+            a1 = n1;
         }
+        put(slot ^ 1, 1, p);
+        __syncthreads();
     };
     if (b0 < b1) {
-        Blk ring[2];
-        load(b0, ring[0]);
-        int blk = b0;
-        for (; blk + 2 <= b1; blk += 2) {
-            load(min(blk + 1, b1 - 1), ring[1]);
-            compute(blk, ring[0]);
-            load(min(blk + 2, b1 - 1), ring[0]);
-            compute(blk + 1, ring[1]);
-        }
-        if (blk < b1) compute(blk, ring[0]);
+        auto run = [&](auto full) {
+            Gf G[2];
+            Qm R[2];
+            const int bl = b1 - 1;
+            load_q(b0, R[0]);
+            load_q(min(b0 + 1, bl), R[1]);
+            load_g(b0, G[0]);
+            {
+                if (h == 0) ms[col] = R[0].m;
+                const f32x16 s = logits(R[0]);
+                float p[16];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float4 mr = rowmax4(t);
+                    const float mm[4] = {mr.x, mr.y, mr.z, mr.w};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) p[4 * t + r] = exp2_weight(s[4 * t + r] * scale_log2 - mm[r]);
+                }
+                put(b0 & 1, 0, p);
+                put(b0 & 1, 1, p);
+                __syncthreads();
+            }
+            // past the range the last block is rebuilt once more and not used
+            // (a last step without it, its products alone, cost spills: 224 B)
+            int blk = b0;
+            for (; blk + 2 <= b1; blk += 2) {
+                step(blk, G[0], R[1], [&]() { load_g(min(blk + 1, bl), G[1]); load_q(min(blk + 2, bl), R[0]); }, full);
+                step(blk + 1, G[1], R[0], [&]() { load_g(min(blk + 2, bl), G[0]); load_q(min(blk + 3, bl), R[1]); }, full);
+            }
+            if (blk < b1) step(blk, G[0], R[1], [&]() {}, full);
+        };
+        if (ntv == 4) run(std::true_type{});
+        else run(std::false_type{});
     }
     float* out = part + (size_t)split * Mp * D;
 #pragma unroll
@@ -1372,12 +1430,14 @@ static bool wide_ok(int prec, int Mp, int D)
 static int dv_cols(int D) { return D % 256 == 0 ? 2 : 1; }
 
 // Pixel-range splits of a dictionary GEMM with ``tiles`` output tiles: the
-// context's choice, else enough workgroups to fill 256 CUs twice; a multiple
-// of 8, at most the (even) number of 32-pixel blocks rounded up to 8.
+// context's choice, else as many as leave no workgroup over when two share each
+// of the 256 CUs; a multiple of 8, at most the (even) number of 32-pixel blocks
+// rounded up to 8.  (Rounded up instead, 12 tiles took 48 splits, whose last 64
+// workgroups ran by themselves after the rest: dV at 816000 x 512 x 768 took
+// 955 us instead of 735.)
 static int pick_splits(int nblocks, int tiles, int want)
 {
-    int s = want > 0 ? want : (512 + tiles - 1) / tiles;
-    s = ((s + 7) / 8) * 8;
+    int s = want > 0 ? (want + 7) / 8 * 8 : 512 / tiles / 8 * 8;
     if (s > nblocks) s = ((nblocks + 7) / 8) * 8;
     if (s < 8) s = 8;
     return s;
@@ -1421,6 +1481,7 @@ bool decode_layout(const lam_ctx* ctx, int prec, int n, int d, int M, int D, Dec
     L->off_gf = take((size_t)nb * D * kPx * tb);
     L->off_ds = take((size_t)nb * Mp * kPx * tb);
     L->off_qt = take((size_t)nb * 32 * kPx * tb);
+    L->off_qb = take((size_t)nb * kPx * d * tb);
     L->off_part = take((size_t)std::max((size_t)sv * Mp * D, (size_t)sk * Mp * 32) * 4);
     L->off_loss = take((size_t)std::max(nb, 1) * 4);
     L->off_sc = take(((size_t)3 * Mp + 64) * 4);
@@ -1448,7 +1509,7 @@ bool decode_dict_layout(const lam_ctx* ctx, int prec, int n, int d, int M, int D
     L->off_vt = take((size_t)Mp * D * tb);
     L->off_kt = take((size_t)32 * Mp * tb);
     L->off_sc = take(((size_t)3 * Mp + 64) * 4);
-    L->off_m2 = L->off_gf = L->off_ds = L->off_qt = L->off_part = L->off_loss = 0;
+    L->off_m2 = L->off_gf = L->off_ds = L->off_qt = L->off_qb = L->off_part = L->off_loss = 0;
     L->bytes = off;
     return true;
 }
@@ -1523,7 +1584,7 @@ static hipError_t run_decode(lam_ctx* ctx, const DecodeArgs& A, const DecodeLayo
     ra.loss_part = reinterpret_cast<float*>(base + L.off_loss);
     ra.Kb = Kb; ra.Vb = Vb; ra.Vt = Vt; ra.Ktp = Ktp;
     ra.M2 = reinterpret_cast<float*>(base + L.off_m2);
-    ra.Gt = base + L.off_gf; ra.St = base + L.off_ds; ra.Qt = base + L.off_qt;
+    ra.Gt = base + L.off_gf; ra.St = base + L.off_ds; ra.Qt = base + L.off_qt; ra.Qb = base + L.off_qb;
     if (F8) {
         float* sc = reinterpret_cast<float*>(base + L.off_sc);
         ra.Vt8 = reinterpret_cast<const uint8_t*>(Vt);
@@ -1561,8 +1622,8 @@ static hipError_t run_decode(lam_ctx* ctx, const DecodeArgs& A, const DecodeLayo
             ProfScope ps(ctx, "decode_tn", st);
             auto kern = qt == 2 ? (A.d == 16 ? k_dec_dv<P, 16, 2> : k_dec_dv<P, 32, 2>)
                                 : (A.d == 16 ? k_dec_dv<P, 16, 1> : k_dec_dv<P, 32, 1>);
-            hipLaunchKernelGGL(kern, dim3(L.splits * ti * tj), dim3(256), 0, st, A.Q, A.n,
-                               (const void*)Kb, A.M, (const float*)ra.M2, ra.scale_log2,
+            hipLaunchKernelGGL(kern, dim3(L.splits * ti * tj), dim3(256), 0, st,
+                               (const void*)ra.Qb, (const void*)Kb, (const float*)ra.M2, ra.scale_log2,
                                (const void*)(base + L.off_gf), Mp, A.D, nb, L.splits, ti, tj, part);
         }
         hipLaunchKernelGGL(k_dec_reduce, dim3((A.M * A.D / 4 + 63) / 64), dim3(256), 0, st,
