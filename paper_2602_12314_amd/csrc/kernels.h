@@ -80,13 +80,14 @@ hipError_t ctx_ensure_lds(lam_ctx* ctx, const void* kernel, size_t bytes);
 size_t scan_scratch_words(uint32_t n);
 size_t radix_scratch_words(int bits, uint32_t n_cap);  // n_cap below 2^30
 int radix_passes(int bits, uint32_t n_cap);  // passes launch_radix_sort makes for ``bits`` key bits
-hipError_t launch_excl_scan(const uint32_t* in, const uint32_t* idx, uint32_t n, uint32_t* out,
-                            uint32_t* total, uint32_t* over, uint32_t cap, uint32_t* scratch,
+hipError_t launch_excl_scan(const uint32_t* in, const uint32_t* idx, const uint32_t* n_dev, uint32_t n,
+                            uint32_t* out, uint32_t* total, uint32_t* over, uint32_t cap, uint32_t* scratch,
                             bool zero_scratch, uint32_t* err, hipStream_t st);
 hipError_t launch_radix_sort(const uint32_t* keys_first, uint32_t* keys_a, uint32_t* vals_a,
                              uint32_t* keys_b, uint32_t* vals_b, bool iota_first,
                              const uint32_t* n_dev, uint32_t n_cap, int bits, uint32_t* scratch,
-                             bool zero_scratch, uint32_t* err, bool* in_b, hipStream_t st);
+                             bool zero_scratch, uint32_t* err, bool* in_b, hipStream_t st,
+                             uint32_t* n_kept = nullptr);
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st);
 
 // ------------------------------------------------------------- profiling
@@ -124,9 +125,9 @@ struct RenderLayout {
     int tile_bits;
     bool tile_in_b;  // where the sorted (tile, record) pairs end up
     // [0] pairs needed, [1] overflow flag, [2] / [3] work counters of the
-    // persistent compositing forward / backward, [4] sort wait error
+    // persistent compositing forward / backward, [4] sort wait error, [5] visible records
     uint32_t* counters;
-    float4* rec0;
+    float4* rec0;  // u, v, and the bits of the first tile and of (tiles per row of the footprint, of the view)
     float4* rec1;
     uint2* foot;
     uint32_t* depth_key;  // per-record depth key as projected (kept for inspection)

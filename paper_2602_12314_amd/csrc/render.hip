@@ -44,8 +44,8 @@ __device__ inline float exp_cw(float x)
     return ldexpf(p, (int)k);
 }
 
-// Record outputs: rec0 = (u, v, 0, 0) (the last two words, a low-order part
-// of the screen mean, are zero for a float32 projection), rec1 = (A, B, C,
+// Record outputs: rec0 = (u, v, first tile, tiles per footprint row | tiles per
+// view row << 16) (the last two words as bits, for k_emit), rec1 = (A, B, C,
 // opacity) with power = -0.5 (A dx^2 + C dy^2) - B dx dy, foot = (x0 | x1 << 16,
 // y0 | y1 << 16) the inclusive pixel footprint.
 //
@@ -162,7 +162,6 @@ __global__ __launch_bounds__(256) void k_preprocess(
         foot[r] = make_uint2(0u, 0u);
         return;
     }
-    rec0[r] = make_float4(u, v, 0.0f, 0.0f);
     const float o = 1.0f / (1.0f + exp_cw(-logits[i]));
     rec1[r] = make_float4(c / det, -b / det, a / det, o);
     foot[r] = make_uint2((uint32_t)x0 | ((uint32_t)x1 << 16), (uint32_t)y0 | ((uint32_t)y1 << 16));
@@ -170,6 +169,9 @@ __global__ __launch_bounds__(256) void k_preprocess(
     const int nx = (x1 >> cs.tile_shift_x) - (x0 >> cs.tile_shift_x) + 1;
     const int ny = (y1 >> cs.tile_shift_y) - (y0 >> cs.tile_shift_y) + 1;
     ntiles[r] = (uint32_t)(nx * ny);
+    const int tx0 = x0 >> cs.tile_shift_x, ty0 = y0 >> cs.tile_shift_y;
+    rec0[r] = make_float4(u, v, __uint_as_float((uint32_t)(cam.tile_base + ty0 * cam.tiles_x + tx0)),
+                          __uint_as_float((uint32_t)nx | ((uint32_t)cam.tiles_x << 16)));
 }
 
 // One thread per emitted (tile id, record) pair, so Gaussians covering many
@@ -177,25 +179,24 @@ __global__ __launch_bounds__(256) void k_preprocess(
 // record s with offsets[s] <= o < offsets[s + 1], and is that record's
 // (o - offsets[s])-th tile of its footprint, rows outer.  A workgroup takes
 // chunks of 256 consecutive pairs, a contiguous range of them: every visible
-// record emits at least one pair and culled records (key 0xFFFFFFFF) sort
-// last, so a chunk's pairs belong to a run of at most 256 consecutive
-// records.  The run's offsets are staged in LDS and each thread finds its
+// record emits at least one pair and culled records are not in the sorted
+// list, so a chunk's pairs belong to a run of at most 256 consecutive
+// records (counters[5] of them).  The run's offsets are staged in LDS and each thread finds its
 // record there.  The first record of the workgroup's first chunk is found by
 // rounds of 256 probes, each narrowing the range 256-fold (three rounds for
 // up to 2^24 records instead of one dependent load per halving); that of each
 // later chunk is read off the staged run of the chunk before it, unless the
 // run ends first (then the probes again).
-__global__ __launch_bounds__(256) void k_emit(CamSet cs, int N, uint32_t R,
-                                             const uint32_t* __restrict__ sorted_rec,
+__global__ __launch_bounds__(256) void k_emit(const uint32_t* __restrict__ sorted_rec,
                                              const uint32_t* __restrict__ offsets,
-                                             const uint2* __restrict__ foot,
+                                             const float4* __restrict__ rec0,
                                              const uint32_t* __restrict__ counters, uint32_t cap,
                                              uint32_t* __restrict__ keys,
                                              uint32_t* __restrict__ vals)
 {
     __shared__ uint32_t run[257];
     __shared__ uint32_t next_s0;
-    const uint32_t total = counters[0] < cap ? counters[0] : cap;
+    const uint32_t total = counters[0] < cap ? counters[0] : cap, R = counters[5];
     const uint32_t nchunks = (total + 255) / 256;
     const uint32_t per = (nchunks + gridDim.x - 1) / gridDim.x;
     const uint32_t c0 = blockIdx.x * per;
@@ -234,17 +235,19 @@ __global__ __launch_bounds__(256) void k_emit(CamSet cs, int N, uint32_t R,
             }
             const uint32_t s = s0 + a;
             const uint32_t r = sorted_rec[s];
-            const int cam = (int)(r / (uint32_t)N);
-            int tbase = 0, tx_n = 1;
-            for (int k = 0; k < cs.n; ++k)
-                if (k == cam) { tbase = cs.c[k].tile_base; tx_n = cs.c[k].tiles_x; }
-            const uint2 f = foot[r];
-            const int x0 = (f.x & 0xFFFF) >> cs.tile_shift_x, x1 = (f.x >> 16) >> cs.tile_shift_x;
-            const int y0 = (f.y & 0xFFFF) >> cs.tile_shift_y;
-            const int nx = x1 - x0 + 1;
-            const int k = (int)(o - run[a]);
-            const int ty = y0 + k / nx, tx = x0 + k % nx;
-            keys[o] = (uint32_t)(tbase + ty * tx_n + tx);
+            const float2 z = *reinterpret_cast<const float2*>(&rec0[r].z);
+            const uint32_t first = __float_as_uint(z.x), nx = __float_as_uint(z.y) & 0xFFFFu;
+            // row and column of the footprint's k-th tile: the reciprocal is
+            // within one of k / nx (k is below 2^21)
+            const uint32_t k = o - run[a];
+            uint32_t row = (uint32_t)((float)k * __builtin_amdgcn_rcpf((float)nx));
+            if (row * nx > k) --row;
+            uint32_t colm = k - row * nx;
+            if (colm >= nx) {
+                ++row;
+                colm -= nx;
+            }
+            keys[o] = first + row * (__float_as_uint(z.y) >> 16) + colm;
             vals[o] = r;
         }
         // the next chunk's first record: the largest j with run[j] <= o0 + 256,
@@ -280,13 +283,25 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ key
                                                uint32_t tiles, uint2* __restrict__ ranges)
 {
     const uint32_t n = counters[0] < cap ? counters[0] : cap;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i <= n; i += gridDim.x * blockDim.x) {
-        const uint32_t a = i > 0 ? keys[i - 1] : 0u;
-        const uint32_t b = i < n ? keys[i] : tiles;
-        if (i > 0 && i < n && a == b) continue;
-        if (i > 0 && a < tiles) ranges[a].y = i;
-        for (uint32_t t = i > 0 ? a + 1 : 0u; t < b && t < tiles; ++t) ranges[t] = make_uint2(0u, 0u);
-        if (i < n && b < tiles) ranges[b].x = i;
+    // four boundaries a thread, their keys one 16-byte load
+    for (uint32_t i0 = (blockIdx.x * blockDim.x + threadIdx.x) * 4; i0 <= n; i0 += gridDim.x * blockDim.x * 4) {
+        uint32_t k[5];
+        k[0] = i0 > 0 ? keys[i0 - 1] : 0u;
+        if (i0 + 4 <= n) {
+            const uint4 v = *reinterpret_cast<const uint4*>(keys + i0);
+            k[1] = v.x; k[2] = v.y; k[3] = v.z; k[4] = v.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) k[j + 1] = i0 + j < n ? keys[i0 + j] : tiles;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t i = i0 + j, a = k[j], b = k[j + 1];
+            if (i > n || (i > 0 && i < n && a == b)) continue;
+            if (i > 0 && a < tiles) ranges[a].y = i;
+            for (uint32_t t = i > 0 ? a + 1 : 0u; t < b && t < tiles; ++t) ranges[t] = make_uint2(0u, 0u);
+            if (i < n && b < tiles) ranges[b].x = i;
+        }
     }
 }
 
@@ -1304,18 +1319,18 @@ hipError_t render_forward_launch(lam_ctx* ctx, const RenderArgs& A, const Render
     {
         ProfScope ps(ctx, "render_sort", st);
         e = launch_radix_sort(L.depth_key, L.depth_a, L.recs_a, L.depth_b, L.recs_b, true, nullptr,
-                              R, 32, L.sort_scratch, false, L.counters + 4, &in_b, st);
+                              R, 32, L.sort_scratch, false, L.counters + 4, &in_b, st, L.counters + 5);
         if (e != hipSuccess) return e;
         const uint32_t* sorted_rec = in_b ? L.recs_b : L.recs_a;
         // pair offsets of the depth-ordered records; the last tile of the scan
         // writes the pairs needed and the overflow flag
-        e = launch_excl_scan(L.ntiles, sorted_rec, R, L.offsets, L.counters, L.counters + 1, cap,
+        e = launch_excl_scan(L.ntiles, sorted_rec, L.counters + 5, R, L.offsets, L.counters, L.counters + 1, cap,
                              L.scan_scratch, false, L.counters + 4, st);
         if (e != hipSuccess) return e;
         if (R > 0 && cap > 0)
             hipLaunchKernelGGL(k_emit, dim3(std::min<uint32_t>((cap + 255) / 256, 8192u)), dim3(256),
-                               0, st, cs, A.n, R, sorted_rec, (const uint32_t*)L.offsets,
-                               (const uint2*)L.foot, (const uint32_t*)L.counters, cap, L.ikeys_a,
+                               0, st, sorted_rec, (const uint32_t*)L.offsets,
+                               (const float4*)L.rec0, (const uint32_t*)L.counters, cap, L.ikeys_a,
                                L.ivals_a);
         e = launch_radix_sort(nullptr, L.ikeys_a, L.ivals_a, L.ikeys_b, L.ivals_b, false,
                               L.counters, cap, L.tile_bits, L.tile_scratch, false, L.counters + 4, &in_b,
@@ -1324,7 +1339,7 @@ hipError_t render_forward_launch(lam_ctx* ctx, const RenderArgs& A, const Render
         tkeys = in_b ? L.ikeys_b : L.ikeys_a;
         trecs = in_b ? L.ivals_b : L.ivals_a;
         if (cs.total_tiles > 0)
-            hipLaunchKernelGGL(k_ranges, dim3(std::min<uint32_t>(cap / 256 + 1, 8192u)), dim3(256), 0, st,
+            hipLaunchKernelGGL(k_ranges, dim3(std::min<uint32_t>(cap / 1024 + 1, 8192u)), dim3(256), 0, st,
                                tkeys, (const uint32_t*)L.counters, cap, (uint32_t)cs.total_tiles,
                                L.ranges);
     }

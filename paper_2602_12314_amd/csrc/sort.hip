@@ -231,10 +231,11 @@ size_t scan_scratch_words(uint32_t n) { return 2 + 2 * (size_t)((n + kTile - 1) 
 // workgroup of the last tile writes the grand total to *total and, when over
 // is given, (total > cap) to *over.
 __global__ __launch_bounds__(kTileThreads) void k_scan_lookback(
-    const uint32_t* __restrict__ in, const uint32_t* __restrict__ idx, uint32_t n,
-    uint32_t* __restrict__ out, uint32_t* total, uint32_t* over, uint32_t cap, uint32_t* scratch,
-    uint32_t* err)
+    const uint32_t* __restrict__ in, const uint32_t* __restrict__ idx, const uint32_t* __restrict__ n_dev,
+    uint32_t n_cap, uint32_t* __restrict__ out, uint32_t* total, uint32_t* over, uint32_t cap,
+    uint32_t* scratch, uint32_t* err)
 {
+    const uint32_t n = load_count(n_dev, n_cap);
     __shared__ uint32_t sh[kTileThreads / kWave];
     __shared__ uint32_t carry_sh;
     const uint32_t t = blockIdx.x;
@@ -285,8 +286,8 @@ __global__ void k_scan_empty(uint32_t* total, uint32_t* over)
     if (over) *over = 0u;
 }
 
-hipError_t launch_excl_scan(const uint32_t* in, const uint32_t* idx, uint32_t n, uint32_t* out,
-                            uint32_t* total, uint32_t* over, uint32_t cap, uint32_t* scratch,
+hipError_t launch_excl_scan(const uint32_t* in, const uint32_t* idx, const uint32_t* n_dev, uint32_t n,
+                            uint32_t* out, uint32_t* total, uint32_t* over, uint32_t cap, uint32_t* scratch,
                             bool zero_scratch, uint32_t* err, hipStream_t st)
 {
     if (n == 0) {
@@ -298,7 +299,7 @@ hipError_t launch_excl_scan(const uint32_t* in, const uint32_t* idx, uint32_t n,
         if (e != hipSuccess) return e;
     }
     const uint32_t nt = (n + kTile - 1) / kTile;
-    hipLaunchKernelGGL(k_scan_lookback, dim3(nt), dim3(kTileThreads), 0, st, in, idx, n, out, total,
+    hipLaunchKernelGGL(k_scan_lookback, dim3(nt), dim3(kTileThreads), 0, st, in, idx, n_dev, n, out, total,
                        over, cap, scratch, err ? err : scratch + 1);
     return hipGetLastError();
 }
@@ -308,19 +309,25 @@ hipError_t launch_excl_scan(const uint32_t* in, const uint32_t* idx, uint32_t n,
 // Digit counts of every pass from one read of the keys: ghist[p * BINS + d]
 // gains the number of keys i < n whose digit p (bits p * width .. p * width +
 // width - 1) is d.  Workgroups stride over the key tiles, count in LDS and add
-// each non-zero bin with one atomic.
+// each non-zero bin with one atomic.  With n_kept, keys of kSkipKey are left
+// out and the number of the others is added to *n_kept.
+constexpr uint32_t kSkipKey = 0xFFFFFFFFu;
+
 template <int DB>
 __global__ __launch_bounds__(kTileThreads) void k_radix_hist(const uint32_t* __restrict__ keys,
                                                              const uint32_t* __restrict__ n_dev,
                                                              uint32_t n_cap, int passes, int width,
-                                                             uint32_t* __restrict__ ghist)
+                                                             uint32_t* __restrict__ ghist, uint32_t* n_kept)
 {
     constexpr int BINS = 1 << DB;
     constexpr int MAXP = (32 + DB - 1) / DB;
     __shared__ uint32_t h[MAXP * BINS];
+    __shared__ uint32_t kept_sh;
     const int nbins = passes * BINS;
     for (int k = threadIdx.x; k < nbins; k += kTileThreads) h[k] = 0;
+    if (threadIdx.x == 0) kept_sh = 0u;
     __syncthreads();
+    uint32_t kept = 0u;  // of this wave
     const uint32_t n = load_count(n_dev, n_cap);
     const uint32_t mask = (1u << width) - 1u;
     for (uint32_t base = blockIdx.x * (uint32_t)kTile; base < n; base += gridDim.x * (uint32_t)kTile) {
@@ -332,13 +339,17 @@ __global__ __launch_bounds__(kTileThreads) void k_radix_hist(const uint32_t* __r
         }
 #pragma unroll
         for (int k = 0; k < kTileItems; ++k) {
-            if (base + k * kTileThreads + threadIdx.x >= n) continue;
+            const bool ok = base + k * kTileThreads + threadIdx.x < n && !(n_kept && key[k] == kSkipKey);
+            kept += (uint32_t)__popcll(__ballot(ok));
+            if (!ok) continue;
             for (int p = 0; p < passes; ++p) atomicAdd(&h[p * BINS + ((key[k] >> (p * width)) & mask)], 1u);
         }
     }
+    if (n_kept && (threadIdx.x & (kWave - 1)) == 0 && kept) atomicAdd(&kept_sh, kept);
     __syncthreads();
     for (int k = threadIdx.x; k < nbins; k += kTileThreads)
         if (h[k]) atomicAdd(&ghist[k], h[k]);
+    if (n_kept && threadIdx.x == 0 && kept_sh) atomicAdd(n_kept, kept_sh);
 }
 
 // One stable pass over the digit at bits shift .. shift + width - 1.  The
@@ -347,12 +358,13 @@ __global__ __launch_bounds__(kTileThreads) void k_radix_hist(const uint32_t* __r
 // offsets among the earlier tiles read back by look-back, and the keys and
 // values are placed in LDS in their sorted order inside the tile and written
 // out from there: consecutive threads store consecutive elements of each
-// digit's run, so the global writes are whole runs.
+// digit's run, so the global writes are whole runs.  With skip, keys of
+// kSkipKey are dropped (the output is as long as the others).
 template <int DB, int ITEMS>
 __global__ __launch_bounds__(kTileThreads) void k_radix_pass(
     const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
     uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
-    const uint32_t* __restrict__ n_dev, uint32_t n_cap, int shift, int width,
+    const uint32_t* __restrict__ n_dev, uint32_t n_cap, int shift, int width, int skip,
     const uint32_t* __restrict__ ghist, uint32_t* status, uint32_t* err)
 {
     constexpr int BINS = 1 << DB;
@@ -401,7 +413,7 @@ __global__ __launch_bounds__(kTileThreads) void k_radix_pass(
 #pragma unroll
     for (int s = 0; s < ITEMS; ++s) {
         const uint32_t i = span + s * kWave + lane;
-        const bool ok = i < n;
+        const bool ok = i < n && !(skip && key[s] == kSkipKey);
         const uint32_t dg = (key[s] >> shift) & mask;
         // lanes holding the same digit: intersect the ballots of its bits
         unsigned long long peers = __ballot(ok);
@@ -511,11 +523,13 @@ size_t radix_scratch_words(int bits, uint32_t n_cap)
 // Sorts the ``bits`` low bits of the keys, ping-ponging between the A and B
 // buffers; *in_b tells where the result ended.  keys_first, when given, is the
 // read-only input of the first pass (it is left intact).  With iota_first the
-// first pass takes value = input position instead of vals_a.
+// first pass takes value = input position instead of vals_a.  With n_kept (a
+// zeroed device word, iota_first) keys of 0xFFFFFFFF are dropped by the first
+// pass, the later passes sort the rest, and *n_kept is their number.
 hipError_t launch_radix_sort(const uint32_t* keys_first, uint32_t* keys_a, uint32_t* vals_a,
                              uint32_t* keys_b, uint32_t* vals_b, bool iota_first,
                              const uint32_t* n_dev, uint32_t n_cap, int bits, uint32_t* scratch,
-                             bool zero_scratch, uint32_t* err, bool* in_b, hipStream_t st)
+                             bool zero_scratch, uint32_t* err, bool* in_b, hipStream_t st, uint32_t* n_kept)
 {
     *in_b = false;
     if (n_cap == 0) return hipSuccess;
@@ -534,20 +548,21 @@ hipError_t launch_radix_sort(const uint32_t* keys_first, uint32_t* keys_a, uint3
     // non-zero bins with one atomic each
     const uint32_t hgrid = std::min<uint32_t>((n_cap + kTile - 1) / kTile, 512u);
     hipLaunchKernelGGL((k_radix_hist<kDigitBits>), dim3(hgrid), dim3(kTileThreads), 0, st,
-                       keys_first ? keys_first : keys_a, n_dev, n_cap, plan.passes, plan.width, gh);
+                       keys_first ? keys_first : keys_a, n_dev, n_cap, plan.passes, plan.width, gh, n_kept);
     uint32_t *ki = keys_a, *vi = vals_a, *ko = keys_b, *vo = vals_b;
     for (int p = 0; p < plan.passes; ++p) {
         const uint32_t* kin = (p == 0 && keys_first) ? keys_first : ki;
         const uint32_t* vin = (p == 0 && iota_first) ? (const uint32_t*)nullptr : vi;
         const uint32_t* ghp = gh + (size_t)p * kBins;
         uint32_t* stp = status + (size_t)p * plan.tiles * kBins;
-        const int shift = plan.width * p;
+        const int shift = plan.width * p, skip = n_kept && p == 0;
+        const uint32_t* nd = n_kept && p > 0 ? n_kept : n_dev;
         if (plan.items == 4)
             hipLaunchKernelGGL((k_radix_pass<kDigitBits, 4>), dim3(plan.tiles), dim3(kTileThreads), 0, st,
-                               kin, vin, ko, vo, n_dev, n_cap, shift, plan.width, ghp, stp, err);
+                               kin, vin, ko, vo, nd, n_cap, shift, plan.width, skip, ghp, stp, err);
         else
             hipLaunchKernelGGL((k_radix_pass<kDigitBits, kTileItems>), dim3(plan.tiles), dim3(kTileThreads),
-                               0, st, kin, vin, ko, vo, n_dev, n_cap, shift, plan.width, ghp, stp, err);
+                               0, st, kin, vin, ko, vo, nd, n_cap, shift, plan.width, skip, ghp, stp, err);
         uint32_t* t = ki; ki = ko; ko = t;
         t = vi; vi = vo; vo = t;
         *in_b = !*in_b;
