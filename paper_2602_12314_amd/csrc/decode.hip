@@ -992,32 +992,27 @@ __global__ __launch_bounds__(NW * kWave) void k_dec_rows(RowsArgs a)
     constexpr int PV = NW == 8 ? 8 : pipe_depth<kDeepRing<F8, NT, NPG, NW>>();
     constexpr int PGD = NW == 8 ? 2 : PV;
     static_assert(PGD >= 2 && PV % PGD == 0, "G ring within the V ring");
-    for (int tt = w; tt < ntiles; tt += TT * NW) {
-        bool has[TT];
-        int tj[TT];
+    auto atom_tiles = [&](int tt, auto count) {
+        constexpr int TN = decltype(count)::value;
+        int tj[TN];
 #pragma unroll
-        for (int j = 0; j < TT; ++j) {
-            has[j] = tt + j * NW < ntiles;
-            // a missing tile repeats the first one (multiplied, never used),
-            // which keeps the loop free of branches
-            tj[j] = has[j] ? tt + j * NW : tt;
-        }
-        Frag kf[TT][NQ], kt[TT][2];
+        for (int j = 0; j < TN; ++j) tj[j] = tt + j * NW;
+        Frag kf[TN][NQ], kt[TN][2];
 #pragma unroll
-        for (int j = 0; j < TT; ++j) {
+        for (int j = 0; j < TN; ++j) {
             kload(tj[j], kf[j]);
 #pragma unroll
             for (int c = 0; c < 2; ++c) kt[j][c] = load_frag<P>(Ktp, 0, 2 * tj[j] + c, nca, lane);
         }
-        f32x16 dp[TT][NPG];
+        f32x16 dp[TN][NPG];
 #pragma unroll
-        for (int j = 0; j < TT; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int g = 0; g < NPG; ++g) dp[j][g] = f32x16{};
-        Frag rv[PV][TT], gb[PGD][NPG];
+        Frag rv[PV][TN], gb[PGD][NPG];
         auto vfetch = [&](int c, Frag* v) {
 #pragma unroll
-            for (int j = 0; j < TT; ++j) v[j] = load_frag<P>(Vb, tj[j], c, ncd, lane);
+            for (int j = 0; j < TN; ++j) v[j] = load_frag<P>(Vb, tj[j], c, ncd, lane);
         };
         auto gfetch = [&](int c, Frag* gg) {
 #pragma unroll
@@ -1025,7 +1020,7 @@ __global__ __launch_bounds__(NW * kWave) void k_dec_rows(RowsArgs a)
         };
         auto mma = [&](const Frag* v, const Frag* gg) {
 #pragma unroll
-            for (int j = 0; j < TT; ++j)
+            for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int g = 0; g < NPG; ++g) P::mma(dp[j][g], v[j], gg[g]);
         };
@@ -1048,11 +1043,15 @@ __global__ __launch_bounds__(NW * kWave) void k_dec_rows(RowsArgs a)
             mma(rv[s], gb[s % PGD]);
         }
 #pragma unroll
-        for (int j = 0; j < TT; ++j)
-            if (has[j]) {
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int g = 0; g < NPG; ++g) finish_tile(tj[j], g, dp[j][g], kf[j], kt[j]);
-            }
+            for (int g = 0; g < NPG; ++g) finish_tile(tj[j], g, dp[j][g], kf[j], kt[j]);
+    };
+    // a wave left with one tile takes it alone (with at most 128 atoms every
+    // wave does: 4800 x 64 x 512 in FP32 spent 7 us on a repeated tile)
+    for (int tt = w; tt < ntiles; tt += TT * NW) {
+        if (TT == 1 || tt + NW < ntiles) atom_tiles(tt, std::integral_constant<int, TT>{});
+        else atom_tiles(tt, std::integral_constant<int, 1>{});
     }
     if (!a.dQ) return;
     __syncthreads();  // region X (G) no longer read
@@ -1347,49 +1346,57 @@ __global__ __launch_bounds__(256, P::kBytes == 2 ? 2 : 1) void k_dec_dv(const vo
                     out[(size_t)(i0 + 32 * t + crow(r, h)) * D + j0 + 32 * q + col] = acc[t][q][r];
 }
 
+// One of the dictionary gradients from its split partials:
 // out[i][j] = sum_split part[split][i][j] (+ 2 lambda (K - K0)[i][j] for dK)
 // for i < rows_out, j < cols_out (a multiple of 4); part has ld = ldp columns
-// and rows_p rows per split.  A workgroup covers 64 groups of 4 consecutive
-// outputs; wave w sums the splits w, w + 4, ... with four 16-byte loads in
-// flight, and the four wave sums are added in LDS in a fixed order.
-__global__ __launch_bounds__(256) void k_dec_reduce(const float* __restrict__ part, int splits,
-                                                    int rows_p, int ldp, int rows_out, int cols_out,
-                                                    float* __restrict__ out, const float* __restrict__ K,
-                                                    const float* __restrict__ K0, float two_lambda)
+// and rows_p rows per split.
+struct ReduceArgs {
+    const float* part;
+    int splits, rows_p, ldp, rows_out, cols_out;
+    float* out;
+    const float *K, *K0;  // K0 null: no trust-region term
+    float two_lambda;
+    int blocks;
+};
+
+// A workgroup covers 64 groups of 4 consecutive outputs; wave w sums the splits
+// w, w + 4, ... with four 16-byte loads in flight, and the four wave sums are
+// added in LDS in a fixed order.
+__device__ inline void reduce_splits(const ReduceArgs& a, int block)
 {
     __shared__ float4 sh[4][64];
-    const int c4 = cols_out >> 2;
-    const size_t n4 = (size_t)rows_out * c4;
+    const int c4 = a.cols_out >> 2;
+    const size_t n4 = (size_t)a.rows_out * c4;
     const int g = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const size_t e4 = (size_t)blockIdx.x * 64 + g;
+    const size_t e4 = (size_t)block * 64 + g;
     int i = 0, j = 0;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (e4 < n4) {
         i = (int)(e4 / c4);
         j = (int)(e4 % c4) * 4;
-        const float* p = part + (size_t)i * ldp + j;
-        const size_t ss = (size_t)rows_p * ldp;
-        float4 a[4];
+        const float* p = a.part + (size_t)i * a.ldp + j;
+        const size_t ss = (size_t)a.rows_p * a.ldp;
+        float4 s[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) a[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int u = 0; u < 4; ++u) s[u] = make_float4(0.f, 0.f, 0.f, 0.f);
         int k = wv;
-        for (; k + 12 < splits; k += 16) {
+        for (; k + 12 < a.splits; k += 16) {
             float4 x[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const float4*>(p + (size_t)(k + 4 * u) * ss);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                a[u].x += x[u].x; a[u].y += x[u].y; a[u].z += x[u].z; a[u].w += x[u].w;
+                s[u].x += x[u].x; s[u].y += x[u].y; s[u].z += x[u].z; s[u].w += x[u].w;
             }
         }
-        for (; k < splits; k += 4) {
+        for (; k < a.splits; k += 4) {
             const float4 x = *reinterpret_cast<const float4*>(p + (size_t)k * ss);
-            a[0].x += x.x; a[0].y += x.y; a[0].z += x.z; a[0].w += x.w;
+            s[0].x += x.x; s[0].y += x.y; s[0].z += x.z; s[0].w += x.w;
         }
-        acc.x = (a[0].x + a[1].x) + (a[2].x + a[3].x);
-        acc.y = (a[0].y + a[1].y) + (a[2].y + a[3].y);
-        acc.z = (a[0].z + a[1].z) + (a[2].z + a[3].z);
-        acc.w = (a[0].w + a[1].w) + (a[2].w + a[3].w);
+        acc.x = (s[0].x + s[1].x) + (s[2].x + s[3].x);
+        acc.y = (s[0].y + s[1].y) + (s[2].y + s[3].y);
+        acc.z = (s[0].z + s[1].z) + (s[2].z + s[3].z);
+        acc.w = (s[0].w + s[1].w) + (s[2].w + s[3].w);
     }
     sh[wv][g] = acc;
     __syncthreads();
@@ -1399,42 +1406,50 @@ __global__ __launch_bounds__(256) void k_dec_reduce(const float* __restrict__ pa
                             (s0.z + s1.z) + (s2.z + s3.z), (s0.w + s1.w) + (s2.w + s3.w)};
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const size_t o = (size_t)i * cols_out + j + t;
+            const size_t o = (size_t)i * a.cols_out + j + t;
             float v = r[t];
-            if (K0) v += two_lambda * (K[o] - K0[o]);
-            out[o] = v;
+            if (a.K0) v += a.two_lambda * (a.K[o] - a.K0[o]);
+            a.out[o] = v;
         }
     }
 }
 
-// loss = (1/n) sum_blocks part + lambda ||K - K0||^2: one 1024-thread
-// workgroup, each thread with eight independent loads in flight per round,
-// then a fixed-order tree in LDS (deterministic).
-__global__ __launch_bounds__(1024) void k_dec_loss(const float* __restrict__ part, int nblocks, float inv_n,
-                                                   const float* __restrict__ K, const float* __restrict__ K0,
-                                                   int nk, float lambda, float* __restrict__ loss)
+// loss = (1/n) sum_blocks part + lambda ||K - K0||^2, each thread with eight
+// independent loads in flight per round, then a fixed-order tree in LDS
+// (deterministic).
+struct LossArgs {
+    const float* part;
+    int nblocks;
+    float inv_n;
+    const float *K, *K0;
+    int nk;
+    float lambda;
+    float* loss;  // null: no loss
+};
+
+__device__ inline void sum_loss(const LossArgs& a)
 {
-    __shared__ float sh[1024];
+    __shared__ float sh[256];
     constexpr int U = 8;
     float s[U], tr[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) s[u] = tr[u] = 0.0f;
-    for (int i0 = 0; i0 < nblocks; i0 += 1024 * U) {
+    for (int i0 = 0; i0 < a.nblocks; i0 += 256 * U) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * 1024 + (int)threadIdx.x;
-            const float x = part[i < nblocks ? i : nblocks - 1];  // every load issued, then masked
-            s[u] += i < nblocks ? x : 0.0f;
+            const int i = i0 + u * 256 + (int)threadIdx.x;
+            const float x = a.part[i < a.nblocks ? i : a.nblocks - 1];  // every load issued, then masked
+            s[u] += i < a.nblocks ? x : 0.0f;
         }
     }
-    if (K0 && lambda != 0.f) {
-        for (int i0 = 0; i0 < nk; i0 += 1024 * U) {
+    if (a.K0 && a.lambda != 0.f) {
+        for (int i0 = 0; i0 < a.nk; i0 += 256 * U) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int i = i0 + u * 1024 + (int)threadIdx.x;
-                const int ic = i < nk ? i : nk - 1;
-                const float dlt = K[ic] - K0[ic];
-                tr[u] += i < nk ? dlt * dlt : 0.0f;
+                const int i = i0 + u * 256 + (int)threadIdx.x;
+                const int ic = i < a.nk ? i : a.nk - 1;
+                const float dlt = a.K[ic] - a.K0[ic];
+                tr[u] += i < a.nk ? dlt * dlt : 0.0f;
             }
         }
     }
@@ -1444,13 +1459,28 @@ __global__ __launch_bounds__(1024) void k_dec_loss(const float* __restrict__ par
         ss += s[u];
         tt += tr[u];
     }
-    sh[threadIdx.x] = ss * inv_n + lambda * tt;
+    sh[threadIdx.x] = ss * a.inv_n + a.lambda * tt;
     __syncthreads();
-    for (int o = 512; o > 0; o >>= 1) {
+    for (int o = 128; o > 0; o >>= 1) {
         if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
         __syncthreads();
     }
-    if (threadIdx.x == 0) loss[0] = sh[0];
+    if (threadIdx.x == 0) a.loss[0] = sh[0];
+}
+
+// dV, dK and the loss from their partials, one launch: the first workgroup sums
+// the loss, the next dk.blocks reduce dK, the rest dV.  (As three launches they
+// took 16 us of the 74 us of a 4800 x 64 x 512 call.)
+__global__ __launch_bounds__(256) void k_dec_finish(ReduceArgs dv, ReduceArgs dk, LossArgs ls)
+{
+    const int b = (int)blockIdx.x;
+    if (b == 0) {
+        if (ls.loss) sum_loss(ls);
+    } else if (b <= dk.blocks) {
+        reduce_splits(dk, b - 1);
+    } else {
+        reduce_splits(dv, b - 1 - dk.blocks);
+    }
 }
 
 // ------------------------------------------------------------ host side
@@ -1533,7 +1563,8 @@ bool decode_layout(const lam_ctx* ctx, int prec, int n, int d, int M, int D, Dec
     L->off_ds = take((size_t)nb * Mp * kPx * tb);
     L->off_qt = take((size_t)nb * 32 * kPx * tb);
     L->off_qb = take((size_t)nb * kPx * d * tb);
-    L->off_part = take((size_t)std::max((size_t)sv * Mp * D, (size_t)sk * Mp * 32) * 4);
+    L->off_part = take((size_t)sv * Mp * D * 4);
+    L->off_partk = take((size_t)sk * Mp * 32 * 4);
     L->off_loss = take((size_t)std::max(nb, 1) * 4);
     L->off_sc = take(((size_t)3 * Mp + 64) * 4);
     L->bytes = off;
@@ -1560,7 +1591,7 @@ bool decode_dict_layout(const lam_ctx* ctx, int prec, int n, int d, int M, int D
     L->off_vt = take((size_t)Mp * D * tb);
     L->off_kt = take((size_t)32 * Mp * tb);
     L->off_sc = take(((size_t)3 * Mp + 64) * 4);
-    L->off_m2 = L->off_gf = L->off_ds = L->off_qt = L->off_qb = L->off_part = L->off_loss = 0;
+    L->off_m2 = L->off_gf = L->off_ds = L->off_qt = L->off_qb = L->off_part = L->off_partk = L->off_loss = 0;
     L->bytes = off;
     return true;
 }
@@ -1677,27 +1708,23 @@ static hipError_t run_decode(lam_ctx* ctx, const DecodeArgs& A, const DecodeLayo
                                (const void*)ra.Qb, (const void*)Kb, (const float*)ra.M2, ra.scale_log2,
                                (const void*)(base + L.off_gf), Mp, A.D, nb, L.splits, ti, tj, part);
         }
-        hipLaunchKernelGGL(k_dec_reduce, dim3((A.M * A.D / 4 + 63) / 64), dim3(256), 0, st,
-                           (const float*)part, nb > 0 ? L.splits : 0, Mp, A.D, A.M, A.D, A.dV,
-                           (const float*)nullptr, (const float*)nullptr, 0.0f);
     }
     // dK = dS^T Q (1/sqrt(d) already in dS) + 2 lambda (K - K0)
-    {
+    float* part_k = reinterpret_cast<float*>(base + L.off_partk);
+    if (nb > 0) {
         const int ti = (Mp + 255) / 256, tj = 1;
-        if (nb > 0) {
-            hipLaunchKernelGGL((k_dec_tn<P, 2, 1, 4, 1>), dim3(L.splits_k * ti * tj), dim3(256), 0, st,
-                               (const void*)(base + L.off_ds), Mp, (const void*)(base + L.off_qt), 32, nb,
-                               L.splits_k, ti, tj, part);
-        }
-        const bool tr = mode == MODE_LOSS && A.K0 && A.lambda_tr != 0.0f;
-        hipLaunchKernelGGL(k_dec_reduce, dim3((A.M * A.d / 4 + 63) / 64), dim3(256), 0, st,
-                           (const float*)part, nb > 0 ? L.splits_k : 0, Mp, 32, A.M, A.d, A.dK,
-                           tr ? A.K : (const float*)nullptr, tr ? A.K0 : (const float*)nullptr,
-                           tr ? 2.0f * A.lambda_tr : 0.0f);
+        hipLaunchKernelGGL((k_dec_tn<P, 2, 1, 4, 1>), dim3(L.splits_k * ti * tj), dim3(256), 0, st,
+                           (const void*)(base + L.off_ds), Mp, (const void*)(base + L.off_qt), 32, nb,
+                           L.splits_k, ti, tj, part_k);
     }
-    if (mode == MODE_LOSS)
-        hipLaunchKernelGGL(k_dec_loss, dim3(1), dim3(1024), 0, st, (const float*)ra.loss_part, nb,
-                           ra.inv_n, A.K, A.K0, A.M * A.d, A.K0 ? A.lambda_tr : 0.0f, A.loss);
+    const bool tr = mode == MODE_LOSS && A.K0 && A.lambda_tr != 0.0f;
+    ReduceArgs dv{part, nb > 0 ? L.splits : 0, Mp, A.D, A.M, A.D, A.dV, nullptr, nullptr, 0.0f,
+                  (A.M * A.D / 4 + 63) / 64};
+    ReduceArgs dk{part_k, nb > 0 ? L.splits_k : 0, Mp, 32, A.M, A.d, A.dK, tr ? A.K : nullptr,
+                  tr ? A.K0 : nullptr, tr ? 2.0f * A.lambda_tr : 0.0f, (A.M * A.d / 4 + 63) / 64};
+    LossArgs ls{ra.loss_part, nb, ra.inv_n, A.K, A.K0, A.M * A.d, A.K0 ? A.lambda_tr : 0.0f,
+                mode == MODE_LOSS ? A.loss : nullptr};
+    hipLaunchKernelGGL(k_dec_finish, dim3(1 + dk.blocks + dv.blocks), dim3(256), 0, st, dv, dk, ls);
     return hipGetLastError();
 }
 

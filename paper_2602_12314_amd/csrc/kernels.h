@@ -164,7 +164,7 @@ struct DecodeLayout {
     uint64_t bytes;
     void* base;
     // byte offsets inside the workspace, filled by decode_layout()
-    size_t off_kb, off_vb, off_vt, off_kt, off_gf, off_m2, off_ds, off_qt, off_qb, off_part, off_loss, off_sc;
+    size_t off_kb, off_vb, off_vt, off_kt, off_gf, off_m2, off_ds, off_qt, off_qb, off_part, off_partk, off_loss, off_sc;
     int splits, splits_k;
     bool wide;  // 64-pixel x 8-wave rows workgroups
 };
