@@ -124,7 +124,9 @@ typedef struct lam_ctx lam_ctx;
  *                      0 = 32 pixels with 4 waves (default); 1 = 64 pixels
  *                      with 8 waves, each V fragment feeding two pixel groups
  *                      (BF16 and E4M3 with D a multiple of 256 up to 1024;
- *                      other shapes keep 0).  Results agree to rounding
+ *                      other shapes keep 0).  lam_decode_forward takes 1 by
+ *                      itself on enough pixels (16384) where it is faster
+ *                      (BF16 at D >= 512, E4M3 at D = 1024).  Results agree to rounding
  *                      (the per-pixel sums over the waves split differently).
  *   "decode_splits"    pixel-range splits of the dV GEMM (the larger of the
  *                      two dictionary-gradient GEMMs; a multiple of 8 in

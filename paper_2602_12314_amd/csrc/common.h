@@ -86,6 +86,15 @@ __device__ inline float wave_allsum(float v)
     return v;
 }
 
+// LDS written by some lanes of the wave is read by others after this (one
+// wave's LDS operations complete in order: it only holds the compiler back).
+__device__ inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ inline unsigned lane_id() { return __lane_id(); }
 
 }  // namespace lam

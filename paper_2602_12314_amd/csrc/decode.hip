@@ -129,6 +129,8 @@ __device__ inline typename P::Frag load_frag(const typename P::T* X, int rb, int
 
 // Row stride (elements) of a wave's dS scratch tile [32 pixels][32 atoms + pad].
 constexpr int kScLd = 40;
+// Row stride (floats) of a wave's F tile [32 pixels][32 features + pad].
+constexpr int kFLd = 36;
 
 // Rows [0, nrows) of the transpose of an LDS tile S[pixel][row] (32 pixels,
 // leading dimension ld) written to Dst[row][32 pixels] in HBM, one chunk of 8
@@ -344,7 +346,8 @@ __global__ __launch_bounds__(NW * kWave) void k_dec_rows(RowsArgs a)
     const int lane = threadIdx.x % kWave;
     float* red = reinterpret_cast<float*>(smem);
     T* Wsc = reinterpret_cast<T*>(smem + 4 * NW * BPX * sizeof(float)) + w * kPx * kScLd;
-    T* X = reinterpret_cast<T*>(smem + 4 * NW * BPX * sizeof(float) + NW * kPx * kScLd * sizeof(T));
+    constexpr size_t kScratch = MODE == MODE_INFER && !F8 ? 0 : NW * kPx * kScLd * sizeof(T);
+    T* X = reinterpret_cast<T*>(smem + 4 * NW * BPX * sizeof(float) + kScratch);
     auto rslot = [&](int set, int ww, int g) { return red + (set * NW + ww) * BPX + g * kPx; };
     const int ldp = a.Mp + 8, ldg = a.D + 8;
 
@@ -707,19 +710,30 @@ __global__ __launch_bounds__(NW * kWave) void k_dec_rows(RowsArgs a)
     }
 
     if (MODE == MODE_INFER) {
+        // each 32 x 32 tile of F through the wave's part of region X, so that a
+        // store covers whole 128-byte lines (8 pixels x 32 features) instead of
+        // 32 bytes of 32 rows
+        __syncthreads();  // everyone is done reading P~
+        float* tr = reinterpret_cast<float*>(X) + w * kPx * kFLd;
 #pragma unroll
-        for (int g = 0; g < NPG; ++g) {
-            if (!valid[g]) continue;
+        for (int g = 0; g < NPG; ++g)
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int t = 0; t < NT; ++t) {
 #pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) {
-                    const int dr = 32 * (w * NT + t) + 8 * g4 + 4 * h;
-                    *reinterpret_cast<float4*>(a.F + (size_t)pxg[g] * a.D + dr) =
+                for (int g4 = 0; g4 < 4; ++g4)
+                    *reinterpret_cast<float4*>(tr + col * kFLd + 8 * g4 + 4 * h) =
                         make_float4(acc[t][g][4 * g4], acc[t][g][4 * g4 + 1], acc[t][g][4 * g4 + 2],
                                     acc[t][g][4 * g4 + 3]);
+                wave_sync();
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int row = 8 * i + (lane >> 3), c = 4 * (lane & 7);
+                    const int px = (blk * NPG + g) * kPx + row;
+                    const float4 v = *reinterpret_cast<const float4*>(tr + row * kFLd + c);
+                    if (px < a.n) *reinterpret_cast<float4*>(a.F + (size_t)px * a.D + 32 * (w * NT + t) + c) = v;
                 }
-        }
+                wave_sync();
+            }
         return;
     }
 
@@ -1485,15 +1499,23 @@ __global__ __launch_bounds__(256) void k_dec_finish(ReduceArgs dv, ReduceArgs dk
 
 // ------------------------------------------------------------ host side
 
-// LDS bytes of k_dec_rows with NW waves and NPG 32-pixel groups.
-static size_t rows_lds(int prec, int Mp, int D, int NW, int NPG)
+// LDS bytes of k_dec_rows with NW waves and NPG 32-pixel groups.  Inference
+// holds P~ alone in region X, and the dS staging tiles only as the E4M3 scales'
+// place: two 64-pixel workgroups then share a CU where the registers allow.
+static size_t rows_lds(int prec, int Mp, int D, int NW, int NPG, bool infer = false)
 {
     const size_t tb = prec == LAM_FP32 ? 4 : 2;
     const size_t bpx = (size_t)kPx * NPG;
-    size_t x = std::max(bpx * (Mp + 8) * tb, bpx * (D + 8) * tb);
-    if (prec == LAM_FP8_E4M3) x = std::max(x, 2 * bpx * (Mp + 16));  // the weights' two E4M3 terms
-    x = std::max(x, (size_t)NW * 32 * (bpx + 2) * 4);  // dQ reduction
-    return 4 * NW * bpx * 4 + (size_t)NW * kPx * kScLd * tb + x;
+    size_t x = bpx * (Mp + 8) * tb, scratch = (size_t)NW * kPx * kScLd * tb;
+    if (prec == LAM_FP8_E4M3) x = 2 * bpx * (Mp + 16);  // the weights' two E4M3 terms
+    if (infer) {
+        if (prec != LAM_FP8_E4M3) scratch = 0;
+        x = std::max(x, (size_t)NW * kPx * kFLd * 4);  // F tiles
+    } else {
+        x = std::max(x, bpx * (std::max(Mp, D) + 8) * tb);  // P~ (its place with E4M3 weights too), G
+        x = std::max(x, (size_t)NW * 32 * (bpx + 2) * 4);   // dQ reduction
+    }
+    return 4 * NW * bpx * 4 + scratch + x;
 }
 
 constexpr size_t kMaxLds = 160 * 1024;  // LDS of a gfx950 workgroup
@@ -1506,6 +1528,19 @@ static bool wide_ok(int prec, int Mp, int D)
     return prec != LAM_FP32 && D % 256 == 0 && D / 256 <= max_nt && rows_lds(prec, Mp, D, 8, 2) <= kMaxLds;
 }
 
+
+// Inference takes 64-pixel blocks by itself where they are faster: each V^T
+// fragment feeds two MFMAs, which pays once V^T is long (BF16, us with 32 / 64
+// pixels: 532 / 414 at 307201 x 500 x 768, 2902 / 2170 at 816000 x 1024 x 1024,
+// 190 / 171 at 307200 x 256 x 512, but 49 / 53 at 76800 x 512 x 256; E4M3, whose
+// fragments are half as long: 2874 / 1958 at D = 1024, but 386 / 428 at D = 768),
+// and the pixels have to fill the CUs with such blocks.
+static bool infer_wide(int prec, int n, int Mp, int D)
+{
+    const int least = prec == LAM_BF16 ? 512 : 1024;
+    return prec != LAM_FP32 && D % 256 == 0 && D >= least && D <= 1024 && n >= 256 * 2 * kPx &&
+           rows_lds(prec, Mp, D, 8, 2, true) <= kMaxLds;
+}
 
 // 32-column tiles per wave in the dV GEMM: two when D is a multiple of 256.
 static int dv_cols(int D) { return D % 256 == 0 ? 2 : 1; }
@@ -1602,7 +1637,7 @@ static hipError_t launch_rows(lam_ctx* ctx, const RowsArgs& ra, bool wide, int n
 {
     const int NW = wide ? 8 : 4, NPG = wide ? 2 : 1;
     const int NT = D / (32 * NW);
-    const size_t lds = rows_lds(prec, Mp, D, NW, NPG);
+    const size_t lds = rows_lds(prec, Mp, D, NW, NPG, MODE == MODE_INFER);
 #define LAM_ROWS(NWV, NPGV, NTV, DQV)                                                                \
     if (NW == NWV && NT == NTV && d == DQV) {                                                        \
         auto kern = k_dec_rows<P, NTV, DQV, MODE, F8, NWV, NPGV>;                                     \
@@ -1676,7 +1711,7 @@ static hipError_t run_decode(lam_ctx* ctx, const DecodeArgs& A, const DecodeLayo
     hipError_t e = hipSuccess;
     if (nb > 0) {
         ProfScope ps(ctx, "decode_rows", st);
-        if (mode == MODE_INFER) e = launch_rows<P, MODE_INFER, F8>(ctx, ra, L.wide, nb, A.D, A.d, Mp, A.prec, st);
+        if (mode == MODE_INFER) e = launch_rows<P, MODE_INFER, F8>(ctx, ra, L.wide || infer_wide(A.prec, A.n, Mp, A.D), nb, A.D, A.d, Mp, A.prec, st);
         else if (mode == MODE_LOSS) e = launch_rows<P, MODE_LOSS, F8>(ctx, ra, L.wide, nb, A.D, A.d, Mp, A.prec, st);
         else e = launch_rows<P, MODE_ADJ, F8>(ctx, ra, L.wide, nb, A.D, A.d, Mp, A.prec, st);
         if (e != hipSuccess) return e;

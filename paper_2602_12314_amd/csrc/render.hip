@@ -341,15 +341,6 @@ struct Block {
     unsigned long long rows;
 };
 
-// LDS written by some lanes of the wave is read by others after this (one
-// wave's LDS operations complete in order: it only holds the compiler back).
-__device__ inline void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ inline Block wave_block(const CamSet& cs, const Cam& cam, int tile)
 {
     const int lt = tile - cam.tile_base;

@@ -337,3 +337,24 @@ def test_paper_dictionary_size_2000(prec):
         e = rel_err(to_np(t_), ref[name])
         say(f"  {name} rel err {e:.3e}")
         assert e < (2.5e-2 if prec == "fp8" and name == "dQ" else 1e-2), name
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp8"])
+@pytest.mark.parametrize("n", [256 * 64 - 1, 256 * 64, 256 * 64 + 33])
+@pytest.mark.parametrize("M,D", [(100, 512), (70, 768), (2048, 1024), (130, 1024)])
+def test_inference_block_choice(prec, n, M, D):
+    """Around the pixel count from which inference takes the 64-pixel block by
+    itself, on whole and ragged blocks: the rows agree with those of a call too
+    small for it.  Both sum the same BF16 products in float32; only the softmax
+    normaliser is added up over another number of waves, so the rows differ by
+    a few float32 roundings (bound: 16 of 2^-24 relative to the row)."""
+    from paper_2602_12314_amd import ops
+    g = torch.Generator(device="cuda").manual_seed(n + M)
+    Q = torch.randn((n, 32), device="cuda", generator=g)
+    K = torch.randn((M, 32), device="cuda", generator=g)
+    V = torch.randn((M, D), device="cuda", generator=g)
+    F = ops.Decoder(prec, n, 32, M, D).forward(Q, K, V)
+    rows = torch.cat([torch.arange(64, device="cuda"), torch.arange(n - 97, n, device="cuda")])
+    small = ops.Decoder(prec, rows.numel(), 32, M, D).forward(Q[rows], K, V)
+    err = (F[rows] - small).norm(dim=1) / small.norm(dim=1)
+    assert float(err.max()) <= 16 * 2.0 ** -24, float(err.max())
