@@ -117,8 +117,9 @@ typedef struct lam_ctx lam_ctx;
  *                      0 = one workgroup per tile; 1 = persistent: as many
  *                      workgroups as fit on the device take tiles from a
  *                      counter in the workspace (evens out views of uneven
- *                      size and tiles of uneven list length); 2 = persistent
- *                      only when several cameras are rendered (default 2).
+ *                      size and tiles of uneven list length); 2 = the
+ *                      library's choice (default 2; at present 0, which is
+ *                      the faster one for one view and for several).
  *                      Results are identical in every mode.
  *   "decode_shape"     workgroup shape of the per-pixel decode kernel:
  *                      0 = 32 pixels with 4 waves (default); 1 = 64 pixels

@@ -32,7 +32,7 @@ struct ProfSlot {
 // behind ``mu``, so calls from several host threads on one context are safe.
 struct lam_ctx {
     int device = 0;
-    std::atomic<int> raster_schedule{2};  // 0 per tile, 1 persistent, 2 persistent for several views
+    std::atomic<int> raster_schedule{2};  // 0 per tile, 1 persistent, 2 the library's choice
     std::atomic<int> decode_shape{0};     // 0: 32 pixels x 4 waves, 1: 64 pixels x 8 waves where it fits
     std::atomic<int> decode_splits{0};    // pixel-range splits of the dictionary GEMMs; 0: sized to the device
     std::atomic<int> profile_on{0};
@@ -88,6 +88,10 @@ hipError_t launch_radix_sort(const uint32_t* keys_first, uint32_t* keys_a, uint3
                              const uint32_t* n_dev, uint32_t n_cap, int bits, uint32_t* scratch,
                              bool zero_scratch, uint32_t* err, bool* in_b, hipStream_t st,
                              uint32_t* n_kept = nullptr);
+// The indices of at most kSmallSort keys by (key, index), keys of 0xFFFFFFFF left
+// out; *n_kept (zeroed) is the number of the others.
+constexpr int kSmallSort = 4096;
+hipError_t launch_sort_small(const uint32_t* keys, uint32_t n, uint32_t* sorted, uint32_t* n_kept, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st);
 
 // ------------------------------------------------------------- profiling

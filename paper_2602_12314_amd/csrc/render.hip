@@ -1278,13 +1278,13 @@ hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st)
 
 // ------------------------------------------------------------- scheduling
 
-// The context's tile schedule: 0 one workgroup per tile, 1 persistent, 2
-// persistent when several views are rendered.
-static bool use_persistent(const lam_ctx* ctx, const CamSet& cs)
-{
-    const int mode = ctx->raster_schedule.load();
-    return mode == 1 || (mode == 2 && cs.n > 1);
-}
+// The context's tile schedule: 0 one workgroup per tile, 1 persistent, 2 the
+// library's choice, which is one workgroup per tile: a workgroup's waves walk
+// their blocks independently, and meeting at the queue after every tile costs
+// more than the even spread saves (eight views of uneven size: forward 291
+// against 313 us, backward 943 against 993 us; 640x480: 49 against 58 us, 117
+// against 118 us).
+static bool use_persistent(const lam_ctx* ctx) { return ctx->raster_schedule.load() == 1; }
 
 hipError_t render_forward_launch(lam_ctx* ctx, const RenderArgs& A, const RenderLayout& L, hipStream_t st)
 {
@@ -1309,8 +1309,11 @@ hipError_t render_forward_launch(lam_ctx* ctx, const RenderArgs& A, const Render
     const uint32_t* trecs;
     {
         ProfScope ps(ctx, "render_sort", st);
-        e = launch_radix_sort(L.depth_key, L.depth_a, L.recs_a, L.depth_b, L.recs_b, true, nullptr,
-                              R, 32, L.sort_scratch, false, L.counters + 4, &in_b, st, L.counters + 5);
+        if (R <= (uint32_t)kSmallSort)
+            e = launch_sort_small(L.depth_key, R, L.recs_a, L.counters + 5, st);
+        else
+            e = launch_radix_sort(L.depth_key, L.depth_a, L.recs_a, L.depth_b, L.recs_b, true, nullptr,
+                                  R, 32, L.sort_scratch, false, L.counters + 4, &in_b, st, L.counters + 5);
         if (e != hipSuccess) return e;
         const uint32_t* sorted_rec = in_b ? L.recs_b : L.recs_a;
         // pair offsets of the depth-ordered records; the last tile of the scan
@@ -1335,7 +1338,7 @@ hipError_t render_forward_launch(lam_ctx* ctx, const RenderArgs& A, const Render
                                L.ranges);
     }
     if (cs.total_tiles > 0) {
-        const bool pers = use_persistent(ctx, cs);
+        const bool pers = use_persistent(ctx);
         const int threads = cs.tile_w * cs.tile_h;
         const bool rgbd = A.rgbd;
         auto kern = rgbd ? (A.d == 16 ? (pers ? k_raster_fwd<16, true, true> : k_raster_fwd<16, false, true>)
@@ -1373,7 +1376,7 @@ hipError_t render_backward_launch(lam_ctx* ctx, const RenderArgs& A, const Rende
     }
     const uint32_t* trecs = L.tile_in_b ? L.ivals_b : L.ivals_a;
     if (cs.total_tiles > 0) {
-        const bool pers = use_persistent(ctx, cs);
+        const bool pers = use_persistent(ctx);
         const int threads = cs.tile_w * cs.tile_h;
         auto kern = rgbd ? (A.d == 16 ? (pers ? k_raster_bwd<16, true, true> : k_raster_bwd<16, false, true>)
                                       : (pers ? k_raster_bwd<32, true, true> : k_raster_bwd<32, false, true>))

@@ -572,4 +572,47 @@ hipError_t launch_radix_sort(const uint32_t* keys_first, uint32_t* keys_a, uint3
 
 int radix_passes(int bits, uint32_t n_cap) { return radix_plan(bits, n_cap).passes; }
 
+// ------------------------------------------------------------ small sorts
+
+// Order of at most kSmallSort keys in one launch (the five launches of the radix
+// sort are mostly latency there: 21 us of the 95 us of a 1000-Gaussian call).  A
+// key's place is the number of kept keys before it: a workgroup places 64 keys,
+// four threads to a key, each comparing it with a quarter of all keys in LDS
+// (n^2 comparisons, which is why it stops at kSmallSort).  Result as of
+// launch_radix_sort with n_kept, in one buffer.
+__global__ __launch_bounds__(256) void k_sort_small(const uint32_t* __restrict__ keys, uint32_t n,
+                                                   uint32_t* __restrict__ sorted, uint32_t* n_kept)
+{
+    __shared__ __align__(16) uint32_t sk[kSmallSort];
+    const uint32_t npad = (n + 15u) & ~15u;
+    for (uint32_t i = threadIdx.x; i < npad; i += 256) sk[i] = i < n ? keys[i] : kSkipKey;
+    __syncthreads();
+    const uint32_t rec = blockIdx.x * 64u + (threadIdx.x >> 2), quarter = threadIdx.x & 3u;
+    const uint32_t mine = rec < n ? sk[rec] : kSkipKey;
+    uint32_t rank = 0u, kept = 0u;
+    for (uint32_t j = quarter * 4u; j < npad; j += 16u) {
+        const uint4 k4 = *reinterpret_cast<const uint4*>(sk + j);
+        const uint32_t k[4] = {k4.x, k4.y, k4.z, k4.w};
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            kept += k[q] != kSkipKey ? 1u : 0u;
+            rank += k[q] < mine || (k[q] == mine && j + q < rec) ? 1u : 0u;
+        }
+    }
+    rank += dpp_u<0xB1, 0xF>(rank);  // the four threads of a key: lane ^ 1, lane ^ 2
+    rank += dpp_u<0x4E, 0xF>(rank);
+    kept += dpp_u<0xB1, 0xF>(kept);
+    kept += dpp_u<0x4E, 0xF>(kept);
+    if (quarter == 0u && mine != kSkipKey) sorted[rank] = rec;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *n_kept = kept;
+}
+
+hipError_t launch_sort_small(const uint32_t* keys, uint32_t n, uint32_t* sorted, uint32_t* n_kept, hipStream_t st)
+{
+    if (n > (uint32_t)kSmallSort) return hipErrorInvalidValue;
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_sort_small, dim3((n + 63) / 64), dim3(256), 0, st, keys, n, sorted, n_kept);
+    return hipGetLastError();
+}
+
 }  // namespace lam

@@ -100,3 +100,19 @@ def test_values_that_are_not_finite_stay_with_their_pairs(d, value):
     for name in GRADS:
         a, b = getattr(g1, name)[~blended], getattr(g0, name)[~blended]
         assert bool(torch.isfinite(a).all()) and rel_err(to_np(a), to_np(b)) <= 2e-4, name
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 4095, 4096, 4097])
+def test_depth_order_around_the_small_sort(n):
+    """Both sides of the size from which the records are sorted by radix passes:
+    the binning (tests of whole scenes check it entry by entry) and with it Q
+    against the oracle, with equal depths among the records."""
+    s = _scene(16, n, 11, 0.0)
+    s.means[:, 2] = np.round(s.means[:, 2] * 16) / 16  # ties: by index
+    s.means[n // 3:n // 2, 2] = -1.0                   # culled
+    s.log_scales[:] -= 1.0
+    f = R.render_forward(R.Gaussians.of(s), s.cams)
+    ok = f["margin"] >= AMBIGUOUS
+    _, _, Q, T, _ = _run(s, (16, 16))
+    assert rel_err(to_np(T)[ok], f["T_final"][ok]) <= 1e-4
+    assert rel_err(to_np(Q)[ok], f["Q"][ok]) <= 1e-4
