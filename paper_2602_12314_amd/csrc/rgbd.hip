@@ -113,7 +113,8 @@ static size_t l1_ws_bytes(int n) { return (size_t)l1_blocks(n) * 3 * 4 + 256; }
 // view its own image; L = lambda (1 - mean S).  One workgroup per 16 x 16
 // tile: the tile and a 5-pixel halo of both images sit in LDS, the window is
 // applied separably (rows, then columns) to x, y, x^2, y^2 and x y.  The
-// forward writes, per pixel and channel, dL/dmu_x, dL/dE[x^2] and dL/dE[x y];
+// forward writes, per pixel and channel, dL/dmu_x, dL/dE[x^2] and dL/dE[x y]
+// (nine planes of P: each channel's pass then reads and writes whole lines);
 // the backward applies the (symmetric) window to those maps and forms
 // dL/dx = W*dmu + 2 x W*dExx + y W*dExy.
 
@@ -135,7 +136,7 @@ __device__ inline int ssim_view(const SsimViews& V, int tile)
 }
 
 __global__ __launch_bounds__(256) void k_ssim_fwd(SsimViews V, const float* __restrict__ x,
-                                                  const float* __restrict__ y, float scale,
+                                                  const float* __restrict__ y, float scale, size_t P,
                                                   float* __restrict__ part, float* __restrict__ tsum)
 {
     __shared__ float sx[kSsH][kSsH + 1], sy[kSsH][kSsH + 1];
@@ -200,9 +201,9 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(SsimViews V, const float* __re
             const float S = a1 * a2 * ib;
             ssum += S;
             // scale = dL/dS = -lambda / (3 P)
-            part[9 * p + 3 * c] = scale * ((2.f * my * a2 - 2.f * my * a1) * ib - S * (2.f * mx / b1 - 2.f * mx / b2));
-            part[9 * p + 3 * c + 1] = scale * (-S / b2);
-            part[9 * p + 3 * c + 2] = scale * (2.f * a1 * ib);
+            part[(3 * c) * P + p] = scale * ((2.f * my * a2 - 2.f * my * a1) * ib - S * (2.f * mx / b1 - 2.f * mx / b2));
+            part[(3 * c + 1) * P + p] = scale * (-S / b2);
+            part[(3 * c + 2) * P + p] = scale * (2.f * a1 * ib);
         }
     }
     const float wsum = wave_allsum(ssum);
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(SsimViews V, const float* __re
 
 __global__ __launch_bounds__(256) void k_ssim_bwd(SsimViews V, const float* __restrict__ x,
                                                   const float* __restrict__ y, const float* __restrict__ part,
-                                                  float* __restrict__ d_rgb, int accumulate)
+                                                  size_t P, float* __restrict__ d_rgb, int accumulate)
 {
     __shared__ float sp[3][kSsH][kSsH + 1];
     __shared__ float hq[3][kSsH][kSsT];
@@ -239,9 +240,9 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(SsimViews V, const float* __re
             float a = 0.f, b = 0.f, d = 0.f;
             if (gx >= 0 && gx < W && gy >= 0 && gy < H) {
                 const size_t pp = (size_t)(base + (long long)gy * W + gx);
-                a = part[9 * pp + 3 * c];
-                b = part[9 * pp + 3 * c + 1];
-                d = part[9 * pp + 3 * c + 2];
+                a = part[(3 * c) * P + pp];
+                b = part[(3 * c + 1) * P + pp];
+                d = part[(3 * c + 2) * P + pp];
             }
             sp[0][r][q] = a;
             sp[1][r][q] = b;
@@ -399,11 +400,11 @@ lam_status lam_ssim_loss(lam_ctx* ctx, const float* rgb, const float* rgb_obs, c
     const float inv_total = 1.0f / (3.0f * (float)pixels);
     ProfScope ps(ctx, "ssim", st);
     hipLaunchKernelGGL(k_ssim_fwd, dim3(V.total_tiles), dim3(256), 0, st, V, rgb, rgb_obs, -lambda * inv_total,
-                       part, tsum);
+                       (size_t)pixels, part, tsum);
     hipLaunchKernelGGL(k_ssim_final, dim3(1), dim3(256), 0, st, (const float*)tsum, V.total_tiles, lambda,
                        inv_total, loss);
     hipLaunchKernelGGL(k_ssim_bwd, dim3(V.total_tiles), dim3(256), 0, st, V, rgb, rgb_obs, (const float*)part,
-                       d_rgb, accumulate ? 1 : 0);
+                       (size_t)pixels, d_rgb, accumulate ? 1 : 0);
     return hipGetLastError() == hipSuccess ? LAM_OK : LAM_ERR_HIP;
 }
 
