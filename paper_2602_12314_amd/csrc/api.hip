@@ -118,7 +118,7 @@ lam_status render_layout(int n_gauss, int d, const float* cams, int n_cams, int 
     L->ranges = (uint2*)take((uint64_t)L->cams.total_tiles * 8);
     L->n_contrib = (uint32_t*)take(pixels * 4);
     L->t_final = (float*)take(pixels * 4);
-    L->rec_grad = (float*)take(R * 24);
+    L->rec_grad = (double*)take(R * kRecGrad * 8);
     L->rec_dz = (float*)take(R * 4);
     L->bytes = off;
     return LAM_OK;

@@ -122,6 +122,10 @@ struct RenderArgs {
     float* d_colors = nullptr;
 };
 
+// Stride of a record's six gradient sums, in float64: one 64-byte line each, so
+// that no record's atomics touch two.
+constexpr int kRecGrad = 8;
+
 // Workspace carve-up (all pointers into the caller's buffer).
 struct RenderLayout {
     CamSet cams;
@@ -145,8 +149,10 @@ struct RenderLayout {
     uint2* ranges;
     uint32_t* n_contrib;
     float* t_final;
-    float* rec_grad;
-    float* rec_dz;  // per-record gradient of the rendered depth
+    // per-record sums of the screen-space gradients (6 a record, float64) and of
+    // the gradient of the rendered depth, written by the backward
+    double* rec_grad;
+    float* rec_dz;
 };
 
 hipError_t render_forward_launch(lam_ctx* ctx, const RenderArgs& A, const RenderLayout& L, hipStream_t st);
