@@ -729,7 +729,7 @@ __device__ inline float sum_groups(float x)
 // query gradients and, with RGBD, the depth sums and the colour gradients.
 // Bound by memory: four threads clear one record's 64-byte line.  One launch for
 // two fills (four with RGBD): with the record lines below, 1026 to 983 us for
-// the whole colour and depth pass at 640x480.
+// the whole colour and depth pass at 1200x680.
 __global__ __launch_bounds__(256) void k_clear_grads(const uint32_t* __restrict__ ntiles, size_t records,
                                                      double* __restrict__ rec_grad,
                                                      float* __restrict__ rec_dz,
