@@ -771,10 +771,11 @@ __global__ __launch_bounds__(256) void k_clear_grads(const uint32_t* __restrict_
 //          gradients need by vector operations (as moments about the block's
 //          centre they would also be a product, but small Gaussians away from
 //          the centre then lose digits to cancellation).
-// Per entry and wave about 45 vector operations and 4 DQ MFMA cycles.  What is
-// left of its time at 640x480 (118 us): 22 us are the prologue and the list
-// steps, 26 us the atomics (32 cache lines of them per batch), the rest the
-// walk at two to three waves per SIMD.
+// Per entry and wave about 45 vector operations and 4 DQ MFMA cycles.  Its
+// time at 640x480 is 110 us.  With float32 sums at 24 bytes a record it was 118
+// us, of which 22 us were the prologue and the list steps, 26 us the atomics (32
+// cache lines of them per batch) and the rest the walk at two to three waves per
+// SIMD.
 template <int DQ, bool RGBD>
 __device__ inline void raster_bwd_tile(
     BwdStage& st, const int tile, const CamSet& cs, int N,
@@ -1316,7 +1317,7 @@ hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st)
 // their blocks independently, and meeting at the queue after every tile costs
 // more than the even spread saves (eight views of uneven size: forward 291
 // against 313 us, backward 943 against 993 us; 640x480: 49 against 58 us, 117
-// against 118 us).
+// against 118 us, all with float32 gradient sums).
 static bool use_persistent(const lam_ctx* ctx) { return ctx->raster_schedule.load() == 1; }
 
 hipError_t render_forward_launch(lam_ctx* ctx, const RenderArgs& A, const RenderLayout& L, hipStream_t st)

@@ -116,3 +116,21 @@ def test_depth_order_around_the_small_sort(n):
     _, _, Q, T, _ = _run(s, (16, 16))
     assert rel_err(to_np(T)[ok], f["T_final"][ok]) <= 1e-4
     assert rel_err(to_np(Q)[ok], f["Q"][ok]) <= 1e-4
+
+
+@pytest.mark.parametrize("d", [16, 32])
+@pytest.mark.parametrize("n", [1, 63, 257, 4097])
+def test_each_backward_starts_from_cleared_sums(n, d):
+    """A backward after another of the same forward, whose upstream gradient left
+    values that are not finite in every sum it reached."""
+    s = _scene(d, n, 13, 0.5)
+    px = int(s.cams[0, 0] * s.cams[0, 1])
+    dQ = torch.as_tensor(np.random.default_rng(6).standard_normal((px, d)), dtype=torch.float32, device="cuda")
+    r, g, _, _, first = _run(s, (16, 16), dQ)
+    first = {name: to_np(getattr(first, name)).copy() for name in GRADS}
+    r.backward(g, torch.full_like(dQ, float("nan")))
+    again = r.backward(g, dQ)
+    # the same sums in another order of arrival: both within the gradients' bar
+    for name in GRADS:
+        a = to_np(getattr(again, name))
+        assert np.isfinite(a).all() and rel_err(a, first[name]) <= 2e-4, name
