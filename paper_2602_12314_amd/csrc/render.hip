@@ -684,15 +684,28 @@ struct BwdStage {
     static __device__ int slot(int p, int e) { return chunk(p, e >> 2) + (e & 3); }
 };
 
-// Mean over the 16 lanes of a group, in every lane; zero if it is not finite.
-__device__ inline float mean16(float x)
+// f over the 16 lanes of a group, in every lane.
+template <class F>
+__device__ inline float over16(float x, F f)
 {
-    x += dpp_f<0xB1, 0xF, 0xF, false>(x);   // lane ^ 1
-    x += dpp_f<0x4E, 0xF, 0xF, false>(x);   // lane ^ 2
-    x += dpp_f<0x141, 0xF, 0xF, false>(x);  // the mirror lane of the half row
-    x += dpp_f<0x140, 0xF, 0xF, false>(x);  // the mirror lane of the row
-    x *= 1.0f / 16.0f;
-    return fabsf(x) <= 3.4e38f ? x : 0.0f;
+    x = f(x, dpp_f<0xB1, 0xF, 0xF, false>(x));   // lane ^ 1
+    x = f(x, dpp_f<0x4E, 0xF, 0xF, false>(x));   // lane ^ 2
+    x = f(x, dpp_f<0x141, 0xF, 0xF, false>(x));  // the mirror lane of the half row
+    return f(x, dpp_f<0x140, 0xF, 0xF, false>(x));  // the mirror lane of the row
+}
+
+// A reference for the 16 values x of a lane group that no |x - r| exceeds |x|
+// by: ref, or where that is too far from zero for one of them the one nearest
+// to zero, or zero where they are of both signs.  With first, ref is their
+// mean.  Values that are not finite are left out.
+__device__ inline float reference16(float x, float ref, bool first)
+{
+    const bool ok = fabsf(x) <= 3.4e38f;
+    const float lo = over16(ok ? x : __builtin_inff(), [](float a, float b) { return fminf(a, b); });
+    const float hi = over16(ok ? x : -__builtin_inff(), [](float a, float b) { return fmaxf(a, b); });
+    const float least = lo > 0.0f ? (lo <= 3.4e38f ? lo : 0.0f) : fminf(hi, 0.0f);
+    if (first) ref = over16(ok ? x * (1.0f / 16.0f) : 0.0f, [](float a, float b) { return a + b; });
+    return fabsf(ref - least) <= fabsf(least) ? ref : least;
 }
 
 // Four 16-lane groups by four registers, transposed: register j of lane group
@@ -888,8 +901,14 @@ __device__ inline void raster_bwd_tile(
     // wave's first batch: where the queries share an offset, s - b would lose
     // the digits of it.  With rref = qref . dQ and past = the product of
     // (1 - alpha) of the entries behind, s - b = (s' - b') + rref past.
-    bool have_ref = false;
+    // The entries of a batch need not share a pixel, and q - qref rounds to the
+    // digits of the larger: so that no query costs another one digits, each
+    // channel of qref is held to where |q - qref| <= |q| for every query so
+    // far (reference16), and a batch that it does not fit moves it.
+    bool first_ref = true;
     float qref[KX], rref = 0.0f, past = 1.0f;
+#pragma unroll
+    for (int k = 0; k < KX; ++k) qref[k] = 0.0f;
 
     // The sums of a batch are added to memory once the next batch's queries are
     // requested: memory operations complete in order, so a load issued after
@@ -944,13 +963,17 @@ __device__ inline void raster_bwd_tile(
             asm volatile("" : "+v"(og[e]));
             if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        if (!have_ref) {  // the wave's first batch: its mean query, and the pixels' dot products with it
-            have_ref = true;
+        bool far = first_ref;
+#pragma unroll
+        for (int k = 0; k < KX; ++k) far |= fabsf(qv[k] - qref[k]) > fabsf(qv[k]);
+        if (__ballot(far) != 0ull) {
             float sv[kBatch];
 #pragma unroll
-            for (int k = 0; k < KD; ++k) qref[k] = mean16(qv[k]);
-            if constexpr (RGBD) qref[KD] = mean16(qv[KD]);
+            for (int k = 0; k < KX; ++k) qref[k] = reference16(qv[k], qref[k], first_ref);
+            first_ref = false;
             dots(qref, sv);
+            // b' relative to the new reference (past = 1: nothing behind yet)
+            behind += past < 1.0f ? (rref - sv[0]) * (1.0f - past) : 0.0f;
             rref = sv[0];
         }
 #pragma unroll
@@ -1101,10 +1124,12 @@ __device__ inline void raster_bwd_tile(
         nq += __popcll(kept);
         if (end <= kList && (nq & (kBatch - 1)) != 0) {
             // the last list step: fill the last batch with entries of no pixel
+            // (the last entry's record, so that no other query is read)
             const int pad = kBatch - (nq & (kBatch - 1));
+            wave_sync();
             if (lane < pad) {
                 st.ab[nq + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-                st.cd[nq + lane] = make_float4(0.f, 1.f, 0.f, __uint_as_float(rbase));
+                st.cd[nq + lane] = make_float4(0.f, 1.f, 0.f, st.cd[nq - 1].w);
                 st.mask[nq + lane] = make_uint2(0u, 0u);
             }
             nq += pad;

@@ -134,3 +134,126 @@ def test_each_backward_starts_from_cleared_sums(n, d):
     for name in GRADS:
         a = to_np(getattr(again, name))
         assert np.isfinite(a).all() and rel_err(a, first[name]) <= 2e-4, name
+
+
+def _run_rgbd(s, col, dQ=None, d_rgb=None, d_depth=None, queries=None, tile=(16, 16)):
+    """(Q, rgb, depth, T) and, with upstream gradients, the gradients by name."""
+    from paper_2602_12314_amd import ops
+    g = ops.Gaussians.from_numpy(s)
+    if queries is not None:
+        g.queries = queries
+    r = ops.Renderer(s.cams, s.n, s.spec.d, tile=tile)
+    maps = r.forward_rgbd(g, col)
+    if dQ is None:
+        return maps, None
+    out, d_colors = r.backward_rgbd(g, col, dQ, d_rgb, d_depth)
+    return maps, dict({name: getattr(out, name) for name in GRADS}, colors=d_colors)
+
+
+def _upstream(n, d, seed, ok=None):
+    rng = np.random.default_rng(seed)
+    out = [rng.standard_normal(shape).astype(np.float32) for shape in ((n, d), (n, 3), (n,))]
+    if ok is not None:
+        for a in out:
+            a[~ok] = 0.0
+    return out
+
+
+def _backward(s, queries, colors, up, rgbd):
+    """Gradients by name for these queries and colours (numpy float32)."""
+    dev = lambda a: torch.as_tensor(a, device="cuda")
+    if rgbd:
+        return {k: to_np(v) for k, v in
+                _run_rgbd(s, dev(colors), *(dev(a) for a in up), queries=dev(queries))[1].items()}
+    gr = _run(s, (16, 16), dev(up[0]), queries=dev(queries))[4]
+    return {k: to_np(getattr(gr, k)) for k in GRADS}
+
+
+def _oracle_backward(s, queries, colors, up, rgbd):
+    g = R.Gaussians.of(s)
+    d = s.spec.d
+    g.queries = np.ascontiguousarray(np.concatenate([queries, colors], axis=1) if rgbd else queries)
+    dmap = np.concatenate(up[:2], axis=1) if rgbd else up[0]
+    ref = R.render_backward(g, s.cams, dmap.astype(np.float64), dZ=up[2].astype(np.float64) if rgbd else None)
+    out = {k: ref[k] for k in GRADS}
+    if rgbd:
+        out["queries"], out["colors"] = ref["queries"][:, :d], ref["queries"][:, d:]
+    return out
+
+
+@pytest.mark.parametrize("rgbd", [False, True])
+@pytest.mark.parametrize("d", [16, 32])
+@pytest.mark.parametrize("value", [1e4, 1e30])
+def test_culled_first_gaussian_takes_no_part(d, value, rgbd):
+    """A few entries per block, so that most batches of the backward are not
+    full, and a Gaussian 0 that no view sees with a large finite query and
+    colour: the others' gradients are the oracle's."""
+    s = _scene(d, 60, 21, 0.5)
+    s.means[0, 2] = -1.0
+    f = R.render_forward(R.Gaussians.of(s), s.cams)
+    ok = f["margin"] >= AMBIGUOUS
+    up = _upstream(ok.size, d, 22, ok)
+    q = s.queries.astype(np.float32)
+    col = np.random.default_rng(23).uniform(0.0, 1.0, (s.n, 3)).astype(np.float32)
+    q[0], col[0] = value, value
+    ref = _oracle_backward(s, q, col, up, rgbd)
+    got = _backward(s, q, col, up, rgbd)
+    for name in ref:
+        assert np.isfinite(got[name]).all(), name
+        assert rel_err(got[name], ref[name]) <= 1e-4, name
+
+
+@pytest.mark.parametrize("rgbd", [False, True])
+@pytest.mark.parametrize("d", [16, 32])
+@pytest.mark.parametrize("value", [1e4, 1e6, 1e30])
+def test_large_values_stay_with_their_pixels(d, value, rgbd):
+    """Small Gaussians, many to a block but seldom two on one pixel, a twentieth
+    of them with queries and colours ``value`` times the others': Gaussians
+    that share no pixel with those have the oracle's gradients."""
+    s = _scene(d, 900, 31, 0.0)
+    rng = np.random.default_rng(32)
+    s.log_scales[:] = rng.uniform(-4.5, -3.5, size=s.log_scales.shape)
+    s.opacity_logits[:] = rng.uniform(-1.0, 4.0, size=s.n)
+    f = R.render_forward(R.Gaussians.of(s), s.cams)
+    ok = f["margin"] >= AMBIGUOUS
+    up = _upstream(ok.size, d, 33, ok)
+    loud = rng.random(s.n) < 0.05
+    mark = np.zeros((s.n, d), np.float32)
+    mark[loud] = 1.0
+    touched = to_np(_run(s, (16, 16), queries=torch.as_tensor(mark, device="cuda"))[2]).any(axis=1)
+    on = np.zeros((ok.size, d), np.float32)
+    on[touched] = 1.0
+    zero = [on, np.zeros((ok.size, 3), np.float32), np.zeros(ok.size, np.float32)]
+    quiet = ~_backward(s, s.queries.astype(np.float32), None, zero, False)["queries"].any(axis=1)
+    assert 0.3 * s.n < quiet.sum() < s.n - loud.sum()
+    q = s.queries.astype(np.float32)
+    col = rng.uniform(0.0, 1.0, (s.n, 3)).astype(np.float32)
+    q[loud] *= np.float32(value)
+    col[loud] *= np.float32(value)
+    ref = _oracle_backward(s, q, col, up, rgbd)
+    got = _backward(s, q, col, up, rgbd)
+    for name in ref:
+        assert np.isfinite(got[name][quiet]).all(), name
+        assert rel_err(got[name][quiet], ref[name][quiet]) <= 1e-4, name
+
+
+@pytest.mark.parametrize("rgbd", [False, True])
+@pytest.mark.parametrize("d", [16, 32])
+def test_common_offset_of_the_queries(d, rgbd):
+    """Opaque pixels and queries (and colours) of unit spread around 1000: the
+    gradient of alpha is a difference of dot products that share the offset's.
+    Rounded each on its own they would lose 1000 x 2^-24 x a few = 2e-4 of it;
+    taken relative to a common query they keep the gradients' bar."""
+    s = _scene(d, 700, 41, 0.5)
+    s.log_scales[:] += 0.5
+    s.opacity_logits[:] = np.random.default_rng(42).uniform(0.0, 4.0, size=s.n)
+    f = R.render_forward(R.Gaussians.of(s), s.cams)
+    ok = (f["margin"] >= AMBIGUOUS) & (f["T_final"] < 1e-2)
+    assert ok.mean() > 0.5
+    up = _upstream(ok.size, d, 43, ok)
+    q = (1000.0 + s.queries).astype(np.float32)
+    col = (1000.0 + np.random.default_rng(44).standard_normal((s.n, 3))).astype(np.float32)
+    ref = _oracle_backward(s, q, col, up, rgbd)
+    got = _backward(s, q, col, up, rgbd)
+    for name in ref:
+        assert rel_err(got[name], ref[name]) <= 1e-4, name
