@@ -257,3 +257,83 @@ def test_common_offset_of_the_queries(d, rgbd):
     got = _backward(s, q, col, up, rgbd)
     for name in ref:
         assert rel_err(got[name], ref[name]) <= 1e-4, name
+
+
+@pytest.mark.parametrize("d", [16, 32])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_rgbd_values_that_are_not_finite_stay_with_their_pairs(d, value):
+    s = _scene(d, 400, 3, 0.5)
+    n = int(s.cams[0, 0] * s.cams[0, 1])
+    col = torch.as_tensor(np.random.default_rng(51).uniform(0.0, 1.0, (s.n, 3)), dtype=torch.float32, device="cuda")
+    (Q0, rgb0, z0, _), _ = _run_rgbd(s, col)
+    who = int(np.argmax(s.opacity_logits + 0.5 * s.log_scales.sum(1)))
+    one = torch.zeros((s.n, d), device="cuda")
+    one[who] = 1.0
+    touched = _run(s, (16, 16), queries=one)[2].abs().sum(1) > 0
+    assert 0 < int(touched.sum()) < n
+    bad = col.clone()
+    bad[who, 1] = value
+    (Q1, rgb1, z1, _), _ = _run_rgbd(s, bad)
+    assert torch.equal(Q1, Q0) and torch.equal(z1, z0)
+    assert torch.equal(~torch.isfinite(rgb1).all(1), touched)
+    assert torch.equal(rgb1[~touched], rgb0[~touched])
+    # an upstream gradient of colour or depth that is not finite at one pixel
+    pix = int(torch.nonzero(touched)[0])
+    up = [torch.as_tensor(a, device="cuda") for a in _upstream(n, d, 52)]
+    only = torch.zeros((n, d), device="cuda")
+    only[pix] = 1.0
+    blended = _run(s, (16, 16), only)[4].queries.abs().sum(1) > 0
+    zero = [a.clone() for a in up]
+    for a in zero:
+        a[pix] = 0.0
+    g0 = _run_rgbd(s, col, *zero)[1]
+    for which in (1, 2):
+        dbad = [a.clone() for a in up]
+        if which == 1:
+            dbad[1][pix, 2] = value
+        else:
+            dbad[2][pix] = value
+        g1 = _run_rgbd(s, col, *dbad)[1]
+        if which == 1:
+            assert torch.equal(~torch.isfinite(g1["colors"]).all(1), blended)
+        else:  # the depth's gradient reaches the means alone
+            assert bool((~torch.isfinite(g1["means"]).all(1))[blended].all())
+        for name in g0:
+            a, b = g1[name][~blended], g0[name][~blended]
+            assert bool(torch.isfinite(a).all()) and rel_err(to_np(a), to_np(b)) <= 2e-4, (which, name)
+
+
+@pytest.mark.parametrize("n", [1, 257, 4097])
+def test_each_rgbd_backward_starts_from_cleared_sums(n):
+    s = _scene(16, n, 13, 0.5)
+    px = int(s.cams[0, 0] * s.cams[0, 1])
+    col = torch.as_tensor(np.random.default_rng(61).uniform(0.0, 1.0, (n, 3)), dtype=torch.float32, device="cuda")
+    up = [torch.as_tensor(a, device="cuda") for a in _upstream(px, 16, 62)]
+    from paper_2602_12314_amd import ops
+    g = ops.Gaussians.from_numpy(s)
+    r = ops.Renderer(s.cams, s.n, 16)
+    r.forward_rgbd(g, col)
+
+    def grads(up):
+        out, dc = r.backward_rgbd(g, col, *up)
+        return dict({name: to_np(getattr(out, name)).copy() for name in GRADS}, colors=to_np(dc).copy())
+
+    first = grads(up)
+    grads([torch.full_like(a, float("nan")) for a in up])
+    again = grads(up)
+    for name in first:
+        assert np.isfinite(again[name]).all() and rel_err(again[name], first[name]) <= 2e-4, name
+
+
+@pytest.mark.parametrize("tile", [(8, 8), (64, 1), (1, 64), (64, 4), (128, 2)])
+def test_rgbd_block_shapes(tile):
+    s = _scene(32, 500, 9, 2.0)
+    n = int(s.cams[0, 0] * s.cams[0, 1])
+    col = torch.as_tensor(np.random.default_rng(71).uniform(0.0, 1.0, (s.n, 3)), dtype=torch.float32, device="cuda")
+    up = [torch.as_tensor(a, device="cuda") for a in _upstream(n, 32, 72)]
+    m0, g0 = _run_rgbd(s, col, *up)
+    m1, g1 = _run_rgbd(s, col, *up, tile=tile)
+    for a, b in zip(m0, m1):
+        assert torch.equal(a, b)
+    for name in g0:  # both within the gradients' bar of the float64 value
+        assert rel_err(to_np(g1[name]), to_np(g0[name])) <= 2e-4, name
