@@ -1278,6 +1278,7 @@ __global__ __launch_bounds__(256, P::kBytes == 2 ? 2 : 1) void k_dec_dv(const vo
     auto step = [&](int blk, const Gf& G, const Qm& next, auto&& request, auto full) {
         const int slot = blk & 1;
         if (h == 0) ms[col] = next.m;
+        wave_sync();  // other lanes read it
         request();  // the operands of the next step
         const f32x16 s = logits(next);
         Frag a0 = afrag(slot, 0, 0), a1 = afrag(slot, 0, 1);
@@ -1324,6 +1325,7 @@ __global__ __launch_bounds__(256, P::kBytes == 2 ? 2 : 1) void k_dec_dv(const vo
             load_g(b0, G[0]);
             {
                 if (h == 0) ms[col] = R[0].m;
+                wave_sync();
                 const f32x16 s = logits(R[0]);
                 float p[16];
 #pragma unroll
