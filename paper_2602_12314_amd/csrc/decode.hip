@@ -1548,14 +1548,21 @@ static bool infer_wide(int prec, int n, int Mp, int D)
 static int dv_cols(int D) { return D % 256 == 0 ? 2 : 1; }
 
 // Pixel-range splits of a dictionary GEMM with ``tiles`` output tiles: the
-// context's choice, else as many as leave no workgroup over when two share each
-// of the 256 CUs; a multiple of 8, at most the (even) number of 32-pixel blocks
-// rounded up to 8.  (Rounded up instead, 12 tiles took 48 splits, whose last 64
-// workgroups ran by themselves after the rest: dV at 816000 x 512 x 768 took
-// 955 us instead of 735.)
-static int pick_splits(int nblocks, int tiles, int want)
+// context's choice, else about as many as let two workgroups share each of the
+// 256 CUs; a multiple of 8, at most the (even) number of 32-pixel blocks
+// rounded up to 8.  On 16-bit operands up to 32 tiles, rounded down, so that no
+// workgroup is left over (48 splits of 12 tiles leave 64 of them to run by
+// themselves: dV at 307200 x 512 x 768 342 us instead of 256; over 9 to 28
+// tiles rounding down takes 0.68 to 0.87 of the time); beyond, 8 and 16 splits
+// are within 6 % of each other, either way.  In FP32 always rounded up: each
+// split's sum is float32, and its length is the error of dV (3.3e-7 against
+// 2.3e-7 from 16 and 24 splits of 100000 pixels; from 16-bit operands it is
+// their rounding, 2e-4, with any number).
+static int pick_splits(int prec, int nblocks, int tiles, int want)
 {
-    int s = want > 0 ? (want + 7) / 8 * 8 : 512 / tiles / 8 * 8;
+    const bool down = prec != LAM_FP32 && tiles <= 32;
+    int s = want > 0 ? want : (512 + (down ? 0 : tiles - 1)) / tiles;
+    s = (want > 0 || !down ? s + 7 : s) / 8 * 8;
     if (s > nblocks) s = ((nblocks + 7) / 8) * 8;
     if (s < 8) s = 8;
     return s;
@@ -1581,8 +1588,8 @@ bool decode_layout(const lam_ctx* ctx, int prec, int n, int d, int M, int D, Dec
     const int tiles_v = ((Mp + 127) / 128) * (D / (128 * dv_cols(D)));
     const int tiles_k = (Mp + 255) / 256;
     // the context may set the dV GEMM's splits (the larger GEMM); dK's keep the rule
-    const int sv = pick_splits(std::max(nb, 1), tiles_v, ctx->decode_splits.load());
-    const int sk = pick_splits(std::max(nb, 1), tiles_k, 0);
+    const int sv = pick_splits(prec, std::max(nb, 1), tiles_v, ctx->decode_splits.load());
+    const int sk = pick_splits(prec, std::max(nb, 1), tiles_k, 0);
     L->splits = sv;
     L->splits_k = sk;
     size_t off = 0;

@@ -187,3 +187,31 @@ def test_kmeans_validation(L):
     st = L.lam_stream_kmeans(None, 1, p, 10, 64, None, None, 0, 3, seeds.ctypes.data_as(C.c_void_p), 3, 2, 2, p, p, p,
                              big, None)
     assert st == _lib.LAM_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("M,D", [(256, 640), (512, 768), (768, 768), (640, 640), (1024, 640), (640, 896), (1024, 1024)])
+def test_fp32_dictionary_sums_are_split_finely_enough(L, M, D):
+    """The FP32 dictionary gradients sum their pixels in float32, so a split's
+    length is their error: no fewer splits than 512 workgroups ask for, rounded
+    up to 8.  Their number is read off the workspace: what is left of it after
+    the buffers that grow with the pixels and the prepared dictionary is one
+    [M, D] and one [M, 32] float32 partial per split."""
+    d, n = 32, 1 << 19
+    assert M % 64 == 0  # no padding atoms
+
+    def size(n):
+        out = C.c_uint64()
+        assert L.lam_decode_workspace_size(None, 0, n, d, M, D, C.byref(out)) == 0
+        return out.value
+
+    def up(tiles):
+        return ((512 + tiles - 1) // tiles + 7) // 8 * 8
+
+    def align(b):
+        return (b + 255) // 256 * 256
+
+    grows = 2 * size(n) - size(2 * n)  # what does not grow with the pixels
+    parts = grows - (M * d + 2 * M * D + 32 * M) * 4 - align((3 * M + 64) * 4)
+    cols = 256 if D % 256 == 0 else 128
+    sv, sk = up(-(-M // 128) * (D // cols)), up(-(-M // 256))
+    assert parts == sv * M * D * 4 + sk * M * 32 * 4
