@@ -323,13 +323,26 @@ constexpr int pipe_depth()
 template <bool F8, int NT, int NPG, int NW>
 constexpr bool kDeepRing = (F8 || NT * NPG > 4) && !(NW == 8 && (NT * NPG >= 8 || (F8 && NT >= 2)));
 
+// Waves per SIMD that the registers of an instance of k_dec_rows are held to
+// (1: as the compiler takes them).  In these it would take two to eight
+// registers more than the next wave allows, and the wave is worth far more
+// (100000 pixels, 256 atoms: 218 -> 147 us for the loss in E4M3 at D = 512,
+// 139 -> 116 us for the inference in BF16 at D = 896).
+template <class P, int NT, int DQ, int MODE, bool F8, int NW>
+constexpr int rows_waves()
+{
+    if (P::kBytes != 2 || NW != 4) return 1;
+    if (MODE == MODE_INFER) return F8 ? 1 : NT == 4 ? 4 : NT == 7 ? 2 : 1;
+    return F8 && (NT == 4 || (MODE == MODE_ADJ && DQ == 16 && (NT == 6 || NT == 7))) ? 2 : 1;
+}
+
 // Workgroup shape of k_dec_rows: NW waves and NPG groups of 32 pixels.  Every
 // wave covers all NPG x 32 pixels of the block and 1 / NW of the D columns
 // (NT = D / (32 NW) tiles of 32) in the F contraction, and the atom tiles
 // w, w + NW, ... in the logits and dP contractions, so each V fragment it loads
 // feeds NPG MFMAs (with NPG = 1, two atom tiles share each G fragment instead).
 template <class P, int NT, int DQ, int MODE, bool F8, int NW, int NPG>
-__global__ __launch_bounds__(NW * kWave) void k_dec_rows(RowsArgs a)
+__global__ __launch_bounds__(NW * kWave, (rows_waves<P, NT, DQ, MODE, F8, NW>())) void k_dec_rows(RowsArgs a)
 {
     using T = typename P::T;
     using Frag = typename P::Frag;
@@ -1006,11 +1019,21 @@ __global__ __launch_bounds__(NW * kWave) void k_dec_rows(RowsArgs a)
     constexpr int PV = NW == 8 ? 8 : pipe_depth<kDeepRing<F8, NT, NPG, NW>>();
     constexpr int PGD = NW == 8 ? 2 : PV;
     static_assert(PGD >= 2 && PV % PGD == 0, "G ring within the V ring");
+    // A wave left with one of TT tiles takes it alone (with at most 128 atoms
+    // every wave does: 4800 x 64 x 512 in FP32 spent 7 us on a repeated tile),
+    // except in BF16 at d = 32 and D <= 512: there the second copy of the loop
+    // costs the registers of a third wave per SIMD (153 -> 189 us at 100000 x
+    // 256 x 512), and the lone tile is multiplied twice, the second time unused.
+    constexpr bool kLone = TT > 1 && (P::kBytes == 4 || F8 || DQ == 16 || NT > 4);
     auto atom_tiles = [&](int tt, auto count) {
         constexpr int TN = decltype(count)::value;
+        bool has[TN];
         int tj[TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) tj[j] = tt + j * NW;
+        for (int j = 0; j < TN; ++j) {
+            has[j] = kLone || tt + j * NW < ntiles;
+            tj[j] = has[j] ? tt + j * NW : tt;
+        }
         Frag kf[TN][NQ], kt[TN][2];
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
@@ -1058,13 +1081,13 @@ __global__ __launch_bounds__(NW * kWave) void k_dec_rows(RowsArgs a)
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j)
+            if (has[j]) {
 #pragma unroll
-            for (int g = 0; g < NPG; ++g) finish_tile(tj[j], g, dp[j][g], kf[j], kt[j]);
+                for (int g = 0; g < NPG; ++g) finish_tile(tj[j], g, dp[j][g], kf[j], kt[j]);
+            }
     };
-    // a wave left with one tile takes it alone (with at most 128 atoms every
-    // wave does: 4800 x 64 x 512 in FP32 spent 7 us on a repeated tile)
     for (int tt = w; tt < ntiles; tt += TT * NW) {
-        if (TT == 1 || tt + NW < ntiles) atom_tiles(tt, std::integral_constant<int, TT>{});
+        if (!kLone || tt + NW < ntiles) atom_tiles(tt, std::integral_constant<int, TT>{});
         else atom_tiles(tt, std::integral_constant<int, 1>{});
     }
     if (!a.dQ) return;
@@ -1646,7 +1669,12 @@ static hipError_t launch_rows(lam_ctx* ctx, const RowsArgs& ra, bool wide, int n
 {
     const int NW = wide ? 8 : 4, NPG = wide ? 2 : 1;
     const int NT = D / (32 * NW);
-    const size_t lds = rows_lds(prec, Mp, D, NW, NPG, MODE == MODE_INFER);
+    // (the inference in FP32 at D = 256 and 384 with 65 to 256 atoms is slower
+    // with the four workgroups on a CU that its own LDS allows than with the two
+    // of the gradient passes': 228 against 208 us at 100000 x 256 x 384, 163
+    // against 154 at D = 256, while 64 atoms at D = 512 gain, 121 -> 88 us)
+    const bool crowded = prec == LAM_FP32 && (D == 256 || D == 384) && Mp > 64 && Mp <= 256;
+    const size_t lds = rows_lds(prec, Mp, D, NW, NPG, MODE == MODE_INFER && !crowded);
 #define LAM_ROWS(NWV, NPGV, NTV, DQV)                                                                \
     if (NW == NWV && NT == NTV && d == DQV) {                                                        \
         auto kern = k_dec_rows<P, NTV, DQV, MODE, F8, NWV, NPGV>;                                     \
