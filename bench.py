@@ -150,7 +150,7 @@ class Workload:
         self.n = sp.n_pixels
         tw, th = (int(v) for v in tile.split("x"))
         self.tune = None
-        self.options = dict(options) if options else {"decode_shape": "px32", "decode_splits": 0}
+        self.options = dict(options) if options else {"decode_shape": "auto", "decode_splits": 0}
         if autotune:
             from paper_2602_12314_amd import autotune as AT
             t0 = time.perf_counter()
@@ -795,7 +795,7 @@ def main():
     ap.add_argument("--no-autotune", action="store_true", help="fixed tile and decode block shape")
     ap.add_argument("--decode-options", default=None, metavar="JSON",
                     help="decode launch options when not autotuned, e.g. "
-                         "'{\"decode_shape\": \"px64\", \"decode_splits\": 0}' (default px32, no split)")
+                         "'{\"decode_shape\": \"px64\", \"decode_splits\": 0}' (default auto, no split)")
     ap.add_argument("--no-oracle", action="store_true", help="skip the FP64 oracle check and CPU baseline")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--eager", action="store_true",

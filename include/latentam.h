@@ -122,13 +122,16 @@ typedef struct lam_ctx lam_ctx;
  *                      the faster one for one view and for several).
  *                      Results are identical in every mode.
  *   "decode_shape"     workgroup shape of the per-pixel decode kernel:
- *                      0 = 32 pixels with 4 waves (default); 1 = 64 pixels
- *                      with 8 waves, each V fragment feeding two pixel groups
- *                      (BF16 and E4M3 with D a multiple of 256 up to 1024;
- *                      other shapes keep 0).  lam_decode_forward takes 1 by
- *                      itself on enough pixels (16384) where it is faster
- *                      (BF16 at D >= 512, E4M3 at D = 1024).  Results agree to rounding
- *                      (the per-pixel sums over the waves split differently).
+ *                      0 = 32 pixels with 4 waves; 1 = 64 pixels with 8
+ *                      waves, each V fragment feeding two pixel groups (BF16
+ *                      and E4M3 with D a multiple of 256 up to 1024; other
+ *                      shapes keep 0); 2 = the library's choice (default):
+ *                      0, and in lam_decode_forward 1 on enough pixels
+ *                      (16384) where it is faster (BF16 at D >= 512, E4M3 at
+ *                      D = 1024).  Results agree to rounding (the per-pixel
+ *                      sums over the waves split differently), so that with 2
+ *                      a row's F may differ by rounding between calls of
+ *                      fewer and of more rows; with 0 or 1 it does not.
  *   "decode_splits"    pixel-range splits of the dV GEMM (the larger of the
  *                      two dictionary-gradient GEMMs; a multiple of 8 in
  *                      [8, 4096], capped at the number of 32-pixel blocks);

@@ -231,7 +231,7 @@ def render_debug_views(ws, n_gauss, d, cams, tile_w, tile_h, capacity, ctx=None)
 
 # ------------------------------------------------------------------ decode
 
-DECODE_SHAPES = {"px32": 0, "px64": 1}
+DECODE_SHAPES = {"px32": 0, "px64": 1, "auto": 2}
 
 
 def decode_workspace_size(precision, n, d, M, D, ctx=None) -> int:

@@ -5,8 +5,8 @@ blended into exactly the pixels of its footprint), so the shape is a pure
 performance choice: ``best_tile`` times render forward + backward for each
 candidate on the caller's own scene and cameras and keeps the fastest.
 ``best_decode_options`` times the decode + loss + gradients call for each
-combination of the context options ``decode_shape`` (32 pixels x 4 waves, 64
-pixels x 8 waves) and ``decode_splits`` (the dV GEMM's pixel-range splits) on
+combination of the context options ``decode_shape`` (``auto``: 32 pixels x 4
+waves in this call; ``px64``: 64 pixels x 8 waves) and ``decode_splits`` (the dV GEMM's pixel-range splits) on
 inputs of the caller's sizes, each under a context of its own; the results
 agree to rounding.  The chosen options are what ``lam_create`` takes as its
 JSON argument (``Context(options=...)``).  Results are cached in JSON keyed by
@@ -27,7 +27,7 @@ import torch
 from . import _lib, ops
 
 CANDIDATES = ((16, 16), (8, 8), (16, 8), (8, 16), (32, 8), (8, 32), (16, 4), (32, 4))
-DECODE_SHAPES = tuple(_lib.DECODE_SHAPES)  # px32, px64
+DECODE_SHAPES = ("auto", "px64")           # auto: 32 pixels here, and the library's choice in inference
 DECODE_SPLITS = (0, 16, 32, 64, 128)       # 0: the library's device-filling rule
 
 

@@ -54,7 +54,7 @@ struct Options {
 bool option_ok(const char* key, long v)
 {
     if (!strcmp(key, "raster_schedule")) return v >= 0 && v <= 2;
-    if (!strcmp(key, "decode_shape")) return v >= 0 && v <= 1;
+    if (!strcmp(key, "decode_shape")) return v >= 0 && v <= 2;
     if (!strcmp(key, "decode_splits")) return v == 0 || (v >= 8 && v <= 4096 && v % 8 == 0);
     return false;
 }
@@ -188,7 +188,7 @@ lam_status lam_create(int device, const char* options_json, lam_ctx** out)
 {
     if (!out) return LAM_ERR_INVALID_ARG;
     *out = nullptr;
-    Options o{2, 0, 0};
+    Options o{2, 2, 0};
     if (!parse_options(options_json, &o)) return LAM_ERR_INVALID_ARG;
     int count = 0;
     if (hipGetDeviceCount(&count) != hipSuccess) return LAM_ERR_HIP;

@@ -1554,7 +1554,7 @@ static bool wide_ok(int prec, int Mp, int D)
 }
 
 
-// Inference takes 64-pixel blocks by itself where they are faster: each V^T
+// Where the choice is the library's, inference takes 64-pixel blocks where they are faster: each V^T
 // fragment feeds two MFMAs, which pays once V^T is long (BF16, us with 32 / 64
 // pixels: 532 / 414 at 307201 x 500 x 768, 2902 / 2170 at 816000 x 1024 x 1024,
 // 190 / 171 at 307200 x 256 x 512, but 49 / 53 at 76800 x 512 x 256; E4M3, whose
@@ -1606,8 +1606,11 @@ bool decode_layout(const lam_ctx* ctx, int prec, int n, int d, int M, int D, Dec
     L->Mp = Mp;
     L->row_blocks = nb;
     // block shape (Same results up to the order of the per-pixel sums over the
-    // waves): 64 pixels x 8 waves where wide_ok allows and the context asks
-    L->wide = ctx->decode_shape.load() == 1 && wide_ok(prec, Mp, D);
+    // waves): 64 pixels x 8 waves where wide_ok allows and the context asks, in
+    // inference also where the context leaves it to infer_wide
+    const int shape = ctx->decode_shape.load();
+    L->wide = shape == 1 && wide_ok(prec, Mp, D);
+    L->wide_infer = L->wide || (shape == 2 && infer_wide(prec, n, Mp, D));
     const int tiles_v = ((Mp + 127) / 128) * (D / (128 * dv_cols(D)));
     const int tiles_k = (Mp + 255) / 256;
     // the context may set the dV GEMM's splits (the larger GEMM); dK's keep the rule
@@ -1748,7 +1751,7 @@ static hipError_t run_decode(lam_ctx* ctx, const DecodeArgs& A, const DecodeLayo
     hipError_t e = hipSuccess;
     if (nb > 0) {
         ProfScope ps(ctx, "decode_rows", st);
-        if (mode == MODE_INFER) e = launch_rows<P, MODE_INFER, F8>(ctx, ra, L.wide || infer_wide(A.prec, A.n, Mp, A.D), nb, A.D, A.d, Mp, A.prec, st);
+        if (mode == MODE_INFER) e = launch_rows<P, MODE_INFER, F8>(ctx, ra, L.wide_infer, nb, A.D, A.d, Mp, A.prec, st);
         else if (mode == MODE_LOSS) e = launch_rows<P, MODE_LOSS, F8>(ctx, ra, L.wide, nb, A.D, A.d, Mp, A.prec, st);
         else e = launch_rows<P, MODE_ADJ, F8>(ctx, ra, L.wide, nb, A.D, A.d, Mp, A.prec, st);
         if (e != hipSuccess) return e;

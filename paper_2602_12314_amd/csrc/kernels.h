@@ -33,7 +33,7 @@ struct ProfSlot {
 struct lam_ctx {
     int device = 0;
     std::atomic<int> raster_schedule{2};  // 0 per tile, 1 persistent, 2 the library's choice
-    std::atomic<int> decode_shape{0};     // 0: 32 pixels x 4 waves, 1: 64 pixels x 8 waves where it fits
+    std::atomic<int> decode_shape{2};     // 0: 32 pixels x 4 waves, 1: 64 pixels x 8 waves where it fits, 2 the library's choice
     std::atomic<int> decode_splits{0};    // pixel-range splits of the dictionary GEMMs; 0: sized to the device
     std::atomic<int> profile_on{0};
     hipEvent_t fork = nullptr;
@@ -176,7 +176,7 @@ struct DecodeLayout {
     // byte offsets inside the workspace, filled by decode_layout()
     size_t off_kb, off_vb, off_vt, off_kt, off_gf, off_m2, off_ds, off_qt, off_qb, off_part, off_partk, off_loss, off_sc;
     int splits, splits_k;
-    bool wide;  // 64-pixel x 8-wave rows workgroups
+    bool wide, wide_infer;  // 64-pixel x 8-wave rows workgroups, in the gradient passes and in inference
 };
 
 // The decode block shape and split count come from the context.

@@ -358,3 +358,34 @@ def test_inference_block_choice(prec, n, M, D):
     small = ops.Decoder(prec, rows.numel(), 32, M, D).forward(Q[rows], K, V)
     err = (F[rows] - small).norm(dim=1) / small.norm(dim=1)
     assert float(err.max()) <= 16 * 2.0 ** -24, float(err.max())
+
+
+@pytest.mark.parametrize("shape", ["px32", "px64"])
+@pytest.mark.parametrize("prec,M,D", [("bf16", 100, 512), ("bf16", 500, 768), ("fp8", 130, 1024)])
+def test_inference_keeps_to_an_explicit_block_shape(prec, M, D, shape):
+    """With the block shape asked for, a row's F is the same bits in a call of
+    so many rows that the library's own choice is the 64-pixel block as in a
+    call of few; and the two shapes, and that choice, differ by rounding only."""
+    from paper_2602_12314_amd import _lib, ops
+    n = 256 * 64 + 33
+    g = torch.Generator(device="cuda").manual_seed(M)
+    Q = torch.randn((n, 32), device="cuda", generator=g)
+    K = torch.randn((M, 32), device="cuda", generator=g)
+    V = torch.randn((M, D), device="cuda", generator=g)
+    rows = torch.cat([torch.arange(64, device="cuda"), torch.arange(n - 97, n, device="cuda")])
+
+    def fwd(opt, q):
+        ctx = _lib.Context(options={"decode_shape": opt})
+        F = ops.Decoder(prec, q.shape[0], 32, M, D, ctx=ctx).forward(q, K, V)
+        torch.cuda.synchronize()
+        ctx.close()
+        return F
+
+    F = fwd(shape, Q)
+    assert torch.equal(F[rows], fwd(shape, Q[rows]))
+    assert torch.equal(fwd("auto", Q), fwd("px64", Q)) and _lib.Context().get("decode_shape") == 2
+    other = fwd("px64" if shape == "px32" else "px32", Q)
+    err = (F - other).norm(dim=1) / other.norm(dim=1)
+    assert float(err.max()) <= 16 * 2.0 ** -24
+    if M > 128:  # up to 128 atoms no wave of either shape has two tiles to add up: the same bits
+        assert float(err.max()) > 0.0
