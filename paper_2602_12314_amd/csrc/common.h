@@ -49,35 +49,12 @@ __device__ inline int cam_of_tile(const CamSet& cs, int tile)
 }
 
 // ---------------------------------------------------------------- wave sums
-// DPP row shifts and row broadcasts; the total of the 64 lanes ends in lane 63.
+// A lane's copy of another's value by a DPP control.
 template <int CTRL, int ROW_MASK, int BANK_MASK, bool BOUND_ZERO>
 __device__ inline float dpp_f(float v)
 {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK,
                                                       BANK_MASK, BOUND_ZERO));
-}
-
-__device__ inline float wave_sum_to_last(float v)
-{
-    v += dpp_f<0x111, 0xF, 0xF, true>(v);   // row_shr:1
-    v += dpp_f<0x112, 0xF, 0xF, true>(v);   // row_shr:2
-    v += dpp_f<0x114, 0xF, 0xE, false>(v);  // row_shr:4, banks 1..3
-    v += dpp_f<0x118, 0xF, 0xC, false>(v);  // row_shr:8, banks 2..3
-    v += dpp_f<0x142, 0xA, 0xF, false>(v);  // row_bcast:15 into rows 1, 3
-    v += dpp_f<0x143, 0xC, 0xF, false>(v);  // row_bcast:31 into rows 2, 3
-    return v;
-}
-
-// Total over the 64 lanes, uniform (all lanes must be active).
-__device__ inline float wave_sum(float v)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_sum_to_last(v)), 63));
-}
-
-__device__ inline float wave_max(float v)
-{
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    return v;
 }
 
 __device__ inline float wave_allsum(float v)
@@ -94,7 +71,5 @@ __device__ inline void wave_sync()
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-
-__device__ inline unsigned lane_id() { return __lane_id(); }
 
 }  // namespace lam

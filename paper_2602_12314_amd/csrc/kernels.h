@@ -74,19 +74,19 @@ hipError_t ctx_ensure_lds(lam_ctx* ctx, const void* kernel, size_t bytes);
 
 // ------------------------------------------------------------- sort / scan
 // The scratch of a scan or a sort must be zero when it starts: the caller
-// clears it (one fill may cover several scratch regions) or passes
-// zero_scratch.  A look-back wait that outlives its bound (never expected)
-// sets *err (a word of the scratch when err is null) and the result is wrong.
+// clears it (one fill may cover several scratch regions).  A look-back wait
+// that outlives its bound (never expected) sets *err (a word of the scratch
+// when err is null) and the result is wrong.
 size_t scan_scratch_words(uint32_t n);
 size_t radix_scratch_words(int bits, uint32_t n_cap);  // n_cap below 2^30
 int radix_passes(int bits, uint32_t n_cap);  // passes launch_radix_sort makes for ``bits`` key bits
 hipError_t launch_excl_scan(const uint32_t* in, const uint32_t* idx, const uint32_t* n_dev, uint32_t n,
                             uint32_t* out, uint32_t* total, uint32_t* over, uint32_t cap, uint32_t* scratch,
-                            bool zero_scratch, uint32_t* err, hipStream_t st);
+                            uint32_t* err, hipStream_t st);
 hipError_t launch_radix_sort(const uint32_t* keys_first, uint32_t* keys_a, uint32_t* vals_a,
                              uint32_t* keys_b, uint32_t* vals_b, bool iota_first,
                              const uint32_t* n_dev, uint32_t n_cap, int bits, uint32_t* scratch,
-                             bool zero_scratch, uint32_t* err, bool* in_b, hipStream_t st,
+                             uint32_t* err, bool* in_b, hipStream_t st,
                              uint32_t* n_kept = nullptr);
 // The indices of at most kSmallSort keys by (key, index), keys of 0xFFFFFFFF left
 // out; *n_kept (zeroed) is the number of the others.

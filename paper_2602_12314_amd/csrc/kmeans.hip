@@ -664,8 +664,8 @@ static hipError_t kmeans_update(const float* X, const float* w, int n, int D, in
     const uint32_t* sidx = nullptr;
     if (n > 0) {
         bool in_b = false;
-        e = launch_radix_sort(a, ka, va, kb, vb, true, nullptr, (uint32_t)n, kmeans_key_bits(k), scratch, false,
-                              nullptr, &in_b, st);
+        e = launch_radix_sort(a, ka, va, kb, vb, true, nullptr, (uint32_t)n, kmeans_key_bits(k), scratch, nullptr,
+                              &in_b, st);
         if (e != hipSuccess) return e;
         skeys = in_b ? kb : ka;
         sidx = in_b ? vb : va;

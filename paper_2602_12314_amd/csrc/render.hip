@@ -1372,13 +1372,13 @@ hipError_t render_forward_launch(lam_ctx* ctx, const RenderArgs& A, const Render
             e = launch_sort_small(L.depth_key, R, L.recs_a, L.counters + 5, st);
         else
             e = launch_radix_sort(L.depth_key, L.depth_a, L.recs_a, L.depth_b, L.recs_b, true, nullptr,
-                                  R, 32, L.sort_scratch, false, L.counters + 4, &in_b, st, L.counters + 5);
+                                  R, 32, L.sort_scratch, L.counters + 4, &in_b, st, L.counters + 5);
         if (e != hipSuccess) return e;
         const uint32_t* sorted_rec = in_b ? L.recs_b : L.recs_a;
         // pair offsets of the depth-ordered records; the last tile of the scan
         // writes the pairs needed and the overflow flag
         e = launch_excl_scan(L.ntiles, sorted_rec, L.counters + 5, R, L.offsets, L.counters, L.counters + 1, cap,
-                             L.scan_scratch, false, L.counters + 4, st);
+                             L.scan_scratch, L.counters + 4, st);
         if (e != hipSuccess) return e;
         if (R > 0 && cap > 0)
             hipLaunchKernelGGL(k_emit, dim3(std::min<uint32_t>((cap + 255) / 256, 8192u)), dim3(256),
@@ -1386,8 +1386,7 @@ hipError_t render_forward_launch(lam_ctx* ctx, const RenderArgs& A, const Render
                                (const float4*)L.rec0, (const uint32_t*)L.counters, cap, L.ikeys_a,
                                L.ivals_a);
         e = launch_radix_sort(nullptr, L.ikeys_a, L.ivals_a, L.ikeys_b, L.ivals_b, false,
-                              L.counters, cap, L.tile_bits, L.tile_scratch, false, L.counters + 4, &in_b,
-                              st);
+                              L.counters, cap, L.tile_bits, L.tile_scratch, L.counters + 4, &in_b, st);
         if (e != hipSuccess) return e;
         tkeys = in_b ? L.ikeys_b : L.ikeys_a;
         trecs = in_b ? L.ivals_b : L.ivals_a;

@@ -288,15 +288,11 @@ __global__ void k_scan_empty(uint32_t* total, uint32_t* over)
 
 hipError_t launch_excl_scan(const uint32_t* in, const uint32_t* idx, const uint32_t* n_dev, uint32_t n,
                             uint32_t* out, uint32_t* total, uint32_t* over, uint32_t cap, uint32_t* scratch,
-                            bool zero_scratch, uint32_t* err, hipStream_t st)
+                            uint32_t* err, hipStream_t st)
 {
     if (n == 0) {
         hipLaunchKernelGGL(k_scan_empty, dim3(1), dim3(1), 0, st, total, over);
         return hipGetLastError();
-    }
-    if (zero_scratch) {
-        hipError_t e = launch_fill_u32(scratch, scan_scratch_words(n), 0u, st);
-        if (e != hipSuccess) return e;
     }
     const uint32_t nt = (n + kTile - 1) / kTile;
     hipLaunchKernelGGL(k_scan_lookback, dim3(nt), dim3(kTileThreads), 0, st, in, idx, n_dev, n, out, total,
@@ -529,16 +525,12 @@ size_t radix_scratch_words(int bits, uint32_t n_cap)
 hipError_t launch_radix_sort(const uint32_t* keys_first, uint32_t* keys_a, uint32_t* vals_a,
                              uint32_t* keys_b, uint32_t* vals_b, bool iota_first,
                              const uint32_t* n_dev, uint32_t n_cap, int bits, uint32_t* scratch,
-                             bool zero_scratch, uint32_t* err, bool* in_b, hipStream_t st, uint32_t* n_kept)
+                             uint32_t* err, bool* in_b, hipStream_t st, uint32_t* n_kept)
 {
     *in_b = false;
     if (n_cap == 0) return hipSuccess;
     if (n_cap >= kMaxSortCount) return hipErrorInvalidValue;
     const RadixPlan plan = radix_plan(bits, n_cap);
-    if (zero_scratch) {
-        hipError_t e = launch_fill_u32(scratch, radix_scratch_words(bits, n_cap), 0u, st);
-        if (e != hipSuccess) return e;
-    }
     if (!err) err = scratch + 4;
     uint32_t* gh = scratch + kRadixHead;
     uint32_t* status = gh + (size_t)plan.passes * kBins;
