@@ -127,8 +127,9 @@ typedef struct lam_ctx lam_ctx;
  *                      and E4M3 with D a multiple of 256 up to 1024; other
  *                      shapes keep 0); 2 = the library's choice (default):
  *                      0, and in lam_decode_forward 1 on enough pixels
- *                      (16384) where it is faster (BF16 at D >= 512, E4M3 at
- *                      D = 1024).  Results agree to rounding (the per-pixel
+ *                      (16384) where it is faster (BF16 at D >= 768, and at
+ *                      D = 512 with 512 atoms or more; E4M3 at D = 1024).
+ *                      Results agree to rounding (the per-pixel
  *                      sums over the waves split differently), so that with 2
  *                      a row's F may differ by rounding between calls of
  *                      fewer and of more rows; with 0 or 1 it does not.

@@ -1554,17 +1554,23 @@ static bool wide_ok(int prec, int Mp, int D)
 }
 
 
-// Where the choice is the library's, inference takes 64-pixel blocks where they are faster: each V^T
-// fragment feeds two MFMAs, which pays once V^T is long (BF16, us with 32 / 64
-// pixels: 532 / 414 at 307201 x 500 x 768, 2902 / 2170 at 816000 x 1024 x 1024,
-// 190 / 171 at 307200 x 256 x 512, but 49 / 53 at 76800 x 512 x 256; E4M3, whose
-// fragments are half as long: 2874 / 1958 at D = 1024, but 386 / 428 at D = 768),
-// and the pixels have to fill the CUs with such blocks.
+// Where the choice is the library's, inference takes 64-pixel blocks where they
+// are faster: each V^T fragment feeds two MFMAs, which pays once V^T is long
+// (us with 32 / 64 pixels: BF16 525 / 417 at 307201 x 500 x 768, E4M3 2874 /
+// 1958 at 816000 x 1024 x 1024 but 386 / 428 at D = 768, whose fragments are
+// half as long) or the atoms are many (BF16 at D = 512: the 64-pixel block
+// takes 0.85 to 0.93 of the time with 512 and 1024 atoms, 0.95 to 1.18 with
+// 256 and fewer), and the pixels have to fill the CUs with such blocks.  In
+// BF16 with fewer than 512 atoms the rounds of 256 blocks have to be full to
+// three quarters: 313 and 516 blocks take 1.00 to 1.12 of the 32-pixel block's
+// time at D = 768 and 1024, 407, 688 and 1875 blocks 0.87 to 0.99.
 static bool infer_wide(int prec, int n, int Mp, int D)
 {
-    const int least = prec == LAM_BF16 ? 512 : 1024;
-    return prec != LAM_FP32 && D % 256 == 0 && D >= least && D <= 1024 && n >= 256 * 2 * kPx &&
-           rows_lds(prec, Mp, D, 8, 2, true) <= kMaxLds;
+    const int blocks = (n + 2 * kPx - 1) / (2 * kPx);
+    if (prec == LAM_FP32 || D % 256 != 0 || D > 1024 || n < 256 * 2 * kPx) return false;
+    if (rows_lds(prec, Mp, D, 8, 2, true) > kMaxLds) return false;
+    if (prec == LAM_FP8_E4M3) return D == 1024;
+    return Mp >= 512 ? D >= 512 : D >= 768 && 4 * blocks >= 3 * 256 * ((blocks + 255) / 256);
 }
 
 // 32-column tiles per wave in the dV GEMM: two when D is a multiple of 256.
