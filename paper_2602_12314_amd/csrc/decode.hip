@@ -170,7 +170,7 @@ __device__ inline void store_pixel_frags(const typename P::T* S, int ld, int nti
 
 // ------------------------------------------------------------ prep
 
-// All four in the fragment-major layout (frag_index), converted to the compute type:
+// All four in the fragment-major layout, converted to the compute type:
 // Kb  = K   [Mp][d]   rows >= M zero
 // Vb  = V   [Mp][D]
 // Vt  = V^T [D][Mp]
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void k_dec_prep(const float* __restrict__ K, c
 {
     const size_t tid = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
-    // inverse of frag_index for an operand with C columns
+    // row and column of element i of a fragment-major operand with C columns
     auto rowk = [](size_t i, int C, int& row, int& k) {
         const int e = (int)(i & 7), lane = (int)((i >> 3) & 63);
         const size_t blk = i >> 9;
@@ -247,8 +247,8 @@ __device__ inline uint8_t to_e4m3(float x)
     return (uint8_t)(__builtin_amdgcn_cvt_pk_fp8_f32(x, 0.0f, 0, false) & 0xFF);
 }
 
-// Vt8 = E4M3(V / s^V) transposed [D][Mp] in the E4M3 fragment-major layout
-// (frag8_index); sv_fold = s^V * 448 / max s^V and unscale = max s^V / 448.
+// Vt8 = E4M3(V / s^V) transposed [D][Mp] in the E4M3 fragment-major layout;
+// sv_fold = s^V * 448 / max s^V and unscale = max s^V / 448.
 // Kb, Vb, Ktp are filled by k_dec_prep<TBF16>.
 __global__ __launch_bounds__(256) void k_dec_prep_fp8(const float* __restrict__ V, int M, int Mp, int D,
                                                       const float* __restrict__ sc, uint8_t* Vt8,

@@ -3,16 +3,19 @@
 // Pipeline of one forward call (one HIP stream, no host synchronisation):
 //   k_preprocess      one thread per (camera, Gaussian) record, float32 projection:
 //                     screen mean, conic, opacity, integer footprint, depth key
-//   radix sort        records by float32 depth bits (stable: ties by record)
+//   sort              visible records by float32 depth bits (stable: ties by
+//                     record): in one launch up to 4096 records, else by radix
 //   scan + k_emit     (tile id, record) pairs emitted in depth order
 //   radix sort        pairs by tile id (stable, so each tile stays depth-ordered)
 //   k_ranges          [start, end) of every tile's list
-//   k_raster_fwd      one workgroup per tile; the tile's list is staged through
-//                     LDS 256 records at a time; each thread blends one pixel
-// The backward walks each pixel's list back to front, rebuilding the
-// transmittance by division, reduces the per-Gaussian terms across the wave
-// with DPP and adds them with one atomic per wave; k_preprocess_bwd chains the
-// screen-space gradients to the raw parameters.
+//   k_raster_fwd      one workgroup per tile, one wave per 64 pixels of it; a
+//                     wave takes the list 64 entries at a time, keeps those that
+//                     reach its pixels and blends them on the matrix cores
+// The backward (k_raster_bwd, after k_clear_grads) walks each pixel's list back
+// to front in batches of 16 entries, rebuilding the transmittance by division,
+// forms the per-Gaussian sums over the wave's pixels by matrix and vector
+// operations and adds them to memory with one atomic per sum and wave;
+// k_preprocess_bwd chains the screen-space gradients to the raw parameters.
 #include "common.h"
 #include "kernels.h"
 
@@ -323,9 +326,9 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ key
 // lane per pixel and the channels in registers, the same sums read every
 // channel of every entry through LDS broadcasts (8 cycles of the CU's one LDS
 // pipe per 16 bytes and wave) and the backward spent most of its vector
-// operations per entry on channels and wave sums.  Measured, before -> now:
-// forward 106 -> 48 us and backward 256 -> 118 us at 640x480 with 100k
-// Gaussians (d = 16), 333 -> 150 us and 830 -> 402 us at 1200x680 with 2M
+// operations per entry on channels and wave sums.  Measured, that -> now:
+// forward 106 -> 49 us and backward 256 -> 112 us at 640x480 with 100k
+// Gaussians (d = 16), 333 -> 152 us and 830 -> 376 us at 1200x680 with 2M
 // (d = 32).
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -764,11 +767,14 @@ __global__ __launch_bounds__(256) void k_clear_grads(const uint32_t* __restrict_
 // rec_grad[r] = (du, dv, dA, dB, dC, dopacity) accumulated over pixels, the sums
 // over the waves in float64: the gradients of a large Gaussian's rotation and
 // scales cancel among the three conic terms, and the rounding of float32 atomics
-// in their order of arrival showed in them (up to 7e-4 of a component from run to
-// run; now the same from run to run).  A record's sums have a 64-byte line of
-// their own, so that its atomics never touch two: the backward of eight views
-// takes 927 us with records of 24 bytes in float32, 1091 us with 48 in float64
-// and 869 us with 64.
+// in their order of arrival showed in them (a component that cancels moved by up
+// to 7e-4 of itself from run to run).  The order is as arbitrary in float64, but
+// seldom survives the rounding to float32: seven runs of four scenes gave the
+// same bits.  The sums of queries, colours and depths (and with the depths'
+// the means' gradient) are float32 and move by up to 3e-6 of the largest.  A
+// record's sums have a 64-byte line of their own, so that its atomics never
+// touch two: the backward of eight views takes 927 us with records of 24 bytes
+// in float32, 1091 us with 48 in float64 and 869 us with 64.
 // With RGBD also d_colors[g] and rec_dz[r] (the gradient of the record's depth).
 //
 // A pixel walks its list back to front, rebuilding the transmittance by
@@ -785,10 +791,10 @@ __global__ __launch_bounds__(256) void k_clear_grads(const uint32_t* __restrict_
 //          centre they would also be a product, but small Gaussians away from
 //          the centre then lose digits to cancellation).
 // Per entry and wave about 45 vector operations and 4 DQ MFMA cycles.  Its
-// time at 640x480 is 110 us.  With float32 sums at 24 bytes a record it was 118
-// us, of which 22 us were the prologue and the list steps, 26 us the atomics (32
-// cache lines of them per batch) and the rest the walk at two to three waves per
-// SIMD.
+// time at 640x480 is 112 us (108 with a reference that any entry could move, see
+// qref below).  With float32 sums at 24 bytes a record it was 118 us, of which 22
+// us were the prologue and the list steps, 26 us the atomics (32 cache lines of
+// them per batch) and the rest the walk at two to three waves per SIMD.
 template <int DQ, bool RGBD>
 __device__ inline void raster_bwd_tile(
     BwdStage& st, const int tile, const CamSet& cs, int N,
