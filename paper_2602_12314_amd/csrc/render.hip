@@ -327,8 +327,8 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ key
 // channel of every entry through LDS broadcasts (8 cycles of the CU's one LDS
 // pipe per 16 bytes and wave) and the backward spent most of its vector
 // operations per entry on channels and wave sums.  Measured, that -> now:
-// forward 106 -> 49 us and backward 256 -> 112 us at 640x480 with 100k
-// Gaussians (d = 16), 333 -> 152 us and 830 -> 376 us at 1200x680 with 2M
+// forward 106 -> 49 us and backward 256 -> 109 us at 640x480 with 100k
+// Gaussians (d = 16), 333 -> 151 us and 830 -> 392 us at 1200x680 with 2M
 // (d = 32).
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -697,18 +697,31 @@ __device__ inline float over16(float x, F f)
     return f(x, dpp_f<0x140, 0xF, 0xF, false>(x));  // the mirror lane of the row
 }
 
-// A reference for the 16 values x of a lane group that no |x - r| exceeds |x|
-// by: ref, or where that is too far from zero for one of them the one nearest
-// to zero, or zero where they are of both signs.  With first, ref is their
-// mean.  Values that are not finite are left out.
-__device__ inline float reference16(float x, float ref, bool first)
+// Whether c holds in a lane of this lane's 16-lane group.
+__device__ inline bool any16(bool c)
+{
+    const unsigned long long m = __ballot(c);
+    const uint32_t h = __lane_id() & 32 ? (uint32_t)(m >> 32) : (uint32_t)m;
+    return ((h >> (__lane_id() & 16)) & 0xFFFFu) != 0u;
+}
+
+// Whether x - ref is larger than x, so that it would round to fewer of x's digits.
+__device__ inline bool too_far(float x, float ref) { return fabsf(x - ref) > fabsf(x); }
+
+// A reference for the 16 values x of a lane group that is too far from none of
+// them: their mean, or where that is too far the one nearest to zero, or zero
+// where they are of both signs.  Values that are not finite are left out.
+__device__ inline float reference16(float x)
 {
     const bool ok = fabsf(x) <= 3.4e38f;
-    const float lo = over16(ok ? x : __builtin_inff(), [](float a, float b) { return fminf(a, b); });
-    const float hi = over16(ok ? x : -__builtin_inff(), [](float a, float b) { return fmaxf(a, b); });
-    const float least = lo > 0.0f ? (lo <= 3.4e38f ? lo : 0.0f) : fminf(hi, 0.0f);
-    if (first) ref = over16(ok ? x * (1.0f / 16.0f) : 0.0f, [](float a, float b) { return a + b; });
-    return fabsf(ref - least) <= fabsf(least) ? ref : least;
+    // magnitudes compare as their bits
+    const float least = over16(fabsf(x), [](float a, float b) {
+        return __uint_as_float(min(__float_as_uint(a), __float_as_uint(b)));
+    });
+    const float mean = over16(ok ? x * (1.0f / 16.0f) : 0.0f, [](float a, float b) { return a + b; });
+    const bool neg = any16(x < 0.0f), pos = any16(x > 0.0f);
+    const float near = neg ? -least : least;
+    return (neg & pos) || least > 3.4e38f ? 0.0f : too_far(near, mean) ? near : mean;
 }
 
 // Four 16-lane groups by four registers, transposed: register j of lane group
@@ -791,8 +804,7 @@ __global__ __launch_bounds__(256) void k_clear_grads(const uint32_t* __restrict_
 //          centre they would also be a product, but small Gaussians away from
 //          the centre then lose digits to cancellation).
 // Per entry and wave about 45 vector operations and 4 DQ MFMA cycles.  Its
-// time at 640x480 is 112 us (108 with a reference that any entry could move, see
-// qref below).  With float32 sums at 24 bytes a record it was 118 us, of which 22
+// time at 640x480 is 109 us.  With float32 sums at 24 bytes a record it was 118 us, of which 22
 // us were the prologue and the list steps, 26 us the atomics (32 cache lines of
 // them per batch) and the rest the walk at two to three waves per SIMD.
 template <int DQ, bool RGBD>
@@ -908,9 +920,11 @@ __device__ inline void raster_bwd_tile(
     // the digits of it.  With rref = qref . dQ and past = the product of
     // (1 - alpha) of the entries behind, s - b = (s' - b') + rref past.
     // The entries of a batch need not share a pixel, and q - qref rounds to the
-    // digits of the larger: so that no query costs another one digits, each
-    // channel of qref is held to where |q - qref| <= |q| for every query so
-    // far (reference16), and a batch that it does not fit moves it.
+    // digits of the larger: so that no query costs another one digits, no
+    // channel of qref is too far from any query visited: reference16 takes it
+    // so for the first batch, and a later query that it does not suit sets that
+    // channel of it to zero (it is then less than half of it or of the other
+    // sign, and there is not much of an offset to keep).
     bool first_ref = true;
     float qref[KX], rref = 0.0f, past = 1.0f;
 #pragma unroll
@@ -971,11 +985,12 @@ __device__ inline void raster_bwd_tile(
         }
         bool far = first_ref;
 #pragma unroll
-        for (int k = 0; k < KX; ++k) far |= fabsf(qv[k] - qref[k]) > fabsf(qv[k]);
+        for (int k = 0; k < KX; ++k) far |= too_far(qv[k], qref[k]);
         if (__ballot(far) != 0ull) {
             float sv[kBatch];
 #pragma unroll
-            for (int k = 0; k < KX; ++k) qref[k] = reference16(qv[k], qref[k], first_ref);
+            for (int k = 0; k < KX; ++k)
+                qref[k] = first_ref ? reference16(qv[k]) : any16(too_far(qv[k], qref[k])) ? 0.0f : qref[k];
             first_ref = false;
             dots(qref, sv);
             // b' relative to the new reference (past = 1: nothing behind yet)
