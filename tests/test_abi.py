@@ -215,3 +215,11 @@ def test_fp32_dictionary_sums_are_split_finely_enough(L, M, D):
     cols = 256 if D % 256 == 0 else 128
     sv, sk = up(-(-M // 128) * (D // cols)), up(-(-M // 256))
     assert parts == sv * M * D * 4 + sk * M * 32 * 4
+
+
+def test_block_shape_values(L):
+    # 0 and 1 are shapes, 2 the library's choice; more is refused before the device is touched
+    out = C.c_void_p()
+    assert L.lam_create(0, b'{"decode_shape": 3}', C.byref(out)) == _lib.LAM_ERR_INVALID_ARG and not out.value
+    assert _lib._encode_options({"decode_shape": "auto"}) == {"decode_shape": 2}
+    assert _lib._encode_options({"decode_shape": "px32"}) == {"decode_shape": 0}
